@@ -517,42 +517,139 @@ attn_merge_kernel(const float* __restrict__ part, uint16_t* __restrict__ out,
                             (size_t)h * HD + d0) = v;
 }
 
-// fp32 path: one thread per (query, head), keys streamed with an online
-// softmax; used by the small fp32 configuration.
+// fp32 path, on the fp32 matrix cores (v_mfma_f32_16x16x4_f32).  A workgroup
+// owns 16 queries of one head; its four wavefronts take 16-key blocks w,
+// w + 4, ... with an online softmax each and are merged through LDS.  Per
+// block a wave forms S^T = K Q^T (lane l: query l % 16, keys 4 (l / 16) + r)
+// from 16-byte loads of K, and O^T += V^T P^T with its scores as the B operand
+// as they stand.  K and V come straight from L2, both before the scores are
+// needed and one block ahead.  Bound by latency at the sizes of this
+// configuration: 192 keys are three blocks per wave (one thread per query
+// walking every key took 320 us there, two thirds of the step).
 template <int D>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(256)
 attn_f32_kernel(const float* __restrict__ qkv, float* __restrict__ out,
                 SeqPack sp, int n_heads, float scale) {
-  const int row = blockIdx.x * 64 + threadIdx.x;
-  if (row >= sp.total) return;
+  constexpr int NB = D / 16;                  // 16-dim blocks of a head
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
   const int h = blockIdx.y;
-  int s = 0;
-  while (s + 1 < sp.n_seqs && sp.row0[s + 1] <= row) ++s;
-  const int r0 = sp.row0[s], r1 = sp.row0[s + 1];
+  // 16-query tile blockIdx.x of the packed batch -> sequence and tile
+  int s = 0, tile = blockIdx.x;
+  for (;; ++s) {
+    const int nt = (sp.row0[s + 1] - sp.row0[s] + 15) / 16;
+    if (tile < nt || s + 1 >= sp.n_seqs) break;
+    tile -= nt;
+  }
+  const int row0 = sp.row0[s], N = sp.row0[s + 1] - row0;
   const int d = n_heads * D;
   const size_t ld = (size_t)3 * d;
-  float qv[D], acc[D];
-  const float* qp = qkv + (size_t)row * ld + (size_t)h * D;
+  const float* base = qkv + (size_t)row0 * ld + (size_t)h * D;
+  f32x4 qv[NB];
+  {
+    const float* qp = base + (size_t)min(tile * 16 + l16, N - 1) * ld + 4 * g;
 #pragma unroll
-  for (int e = 0; e < D; ++e) { qv[e] = qp[e] * scale; acc[e] = 0.f; }
-  float m = -INFINITY, l = 0.f;
-  for (int j = r0; j < r1; ++j) {
-    const float* kp = qkv + (size_t)j * ld + d + (size_t)h * D;
-    float sc = 0.f;
-#pragma unroll
-    for (int e = 0; e < D; ++e) sc = fmaf(qv[e], kp[e], sc);
-    const float mn = fmaxf(m, sc);
-    const float a = expf(m - mn), p = expf(sc - mn);
-    l = l * a + p;
-    const float* vp = qkv + (size_t)j * ld + 2 * d + (size_t)h * D;
-#pragma unroll
-    for (int e = 0; e < D; ++e) acc[e] = acc[e] * a + p * vp[e];
-    m = mn;
+    for (int j = 0; j < NB; ++j)
+      qv[j] = *reinterpret_cast<const f32x4*>(qp + 16 * j) * scale;
   }
-  float* op = out + (size_t)row * d + (size_t)h * D;
-  const float inv = 1.0f / l;
+  f32x4 o[NB];
 #pragma unroll
-  for (int e = 0; e < D; ++e) op[e] = acc[e] * inv;
+  for (int j = 0; j < NB; ++j) o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  const int nb = (N + 15) / 16;
+
+  f32x4 kf[NB], vf[NB];
+  auto load = [&](int kb, f32x4 (&kd)[NB], f32x4 (&vd)[NB]) {
+    const float* kp = base + d + (size_t)min(kb * 16 + l16, N - 1) * ld + 4 * g;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      kd[j] = *reinterpret_cast<const f32x4*>(kp + 16 * j);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float* vp =
+          base + 2 * d + (size_t)min(kb * 16 + 4 * g + r, N - 1) * ld + l16;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) vd[j][r] = vp[16 * j];
+    }
+  };
+  if (wave < nb) load(wave, kf, vf);
+  for (int kb = wave; kb < nb; kb += 4) {
+    f32x4 kn[NB], vn[NB];
+    if (kb + 4 < nb) load(kb + 4, kn, vn);
+    f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < NB; j += 2)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        sa = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][e], qv[j][e], sa, 0, 0, 0);
+        sb = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j + 1][e], qv[j + 1][e], sb,
+                                                  0, 0, 0);
+      }
+    float sc[4], mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      sc[r] = kb * 16 + 4 * g + r < N ? sa[r] + sb[r] : -INFINITY;
+      mx = fmaxf(mx, sc[r]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float mn = fmaxf(m, mx);
+    const float al = expf(m - mn);
+    float p[4], ps = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      p[r] = expf(sc[r] - mn);
+      ps += p[r];
+    }
+    ps += __shfl_xor(ps, 16, 64);
+    ps += __shfl_xor(ps, 32, 64);
+    l = l * al + ps;
+    m = mn;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) o[j] *= al;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        o[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[j][r], p[r], o[j], 0, 0, 0);
+    if (kb + 4 < nb) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j) { kf[j] = kn[j]; vf[j] = vn[j]; }
+    }
+  }
+  // merge the waves: o[j][r] is dim 16 j + 4 g + r of query l16
+  __shared__ float so[4][16][D + 1];
+  __shared__ float sm[4][16], sl[4][16];
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) so[wave][l16][16 * j + 4 * g + r] = o[j][r];
+  if (g == 0) {
+    sm[wave][l16] = m;
+    sl[wave][l16] = l;
+  }
+  __syncthreads();
+  const int q = threadIdx.x >> 4;
+  if (tile * 16 + q >= N) return;
+  const float mm = fmaxf(fmaxf(sm[0][q], sm[1][q]), fmaxf(sm[2][q], sm[3][q]));
+  float w[4], den = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    // a wave without a block has l = 0 and takes no part
+    w[i] = i < nb ? expf(sm[i][q] - mm) : 0.f;
+    den += w[i] * sl[i][q];
+  }
+  const float inv = 1.0f / den;
+  float* op = out + (size_t)(row0 + tile * 16 + q) * d + (size_t)h * D;
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const int dd = 16 * j + (threadIdx.x & 15);
+    float v = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v += w[i] * so[i][q][dd];
+    op[dd] = v * inv;
+  }
 }
 
 }  // namespace
@@ -670,13 +767,16 @@ int launch_attention_f32(const float* qkv, float* o, const SeqPack& sp,
                          int n_heads, int head_dim, hipStream_t s) {
   if (sp.total == 0) return DAVET_OK;
   ProfScope ps(KC_ATTN_F32, s);
-  dim3 grid((sp.total + 63) / 64, n_heads);
+  int tiles = 0;
+  for (int i = 0; i < sp.n_seqs; ++i)
+    tiles += (sp.row0[i + 1] - sp.row0[i] + 15) / 16;
+  dim3 grid(tiles, n_heads);
   const float scale = 1.0f / sqrtf((float)head_dim);
   if (head_dim == 64)
-    hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(64), 0, s, qkv, o, sp,
+    hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(256), 0, s, qkv, o, sp,
                        n_heads, scale);
   else if (head_dim == 128)
-    hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(64), 0, s, qkv, o, sp,
+    hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(256), 0, s, qkv, o, sp,
                        n_heads, scale);
   else
     return set_error(DAVET_ESHAPE, "attention_f32: head_dim must be 64 or 128");

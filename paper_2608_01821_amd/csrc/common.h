@@ -205,8 +205,8 @@ struct RowList {
   int32_t* overflow;      // the step's 16-bit overflow counter (may be null)
   int clear_overflow;     // the list builder zeroes it first
 };
-// assembly + first norm of every packed row; one extra workgroup builds the
-// masked-row list alongside
+// assembly (and, with A given, the first norm) of every packed row; one extra
+// workgroup builds the masked-row list alongside
 int launch_assemble_norm(const SeqPack& sp, const ViewPtrs& vp, int dtype,
                          const void* embed, const int32_t* prompt_ids,
                          const int32_t* resp_ids, const uint8_t* masked,
@@ -217,8 +217,6 @@ int launch_rmsnorm(const float* X, int rows, int d, const float* gain,
                    float eps, int dtype, void* A, hipStream_t s);
 int launch_rope_table(int max_pos, int head_dim, float theta, float* cs,
                       hipStream_t s);
-int launch_rope(void* qkv, int rows, int n_heads, int head_dim, int dtype,
-                const SeqPack& sp, const float* cs, hipStream_t s);
 int launch_final_norm_gather(const float* X, const SeqPack& sp,
                              const int32_t* list, int max_rows, int d,
                              const float* gain, float eps, int dtype, void* Hm,
@@ -284,9 +282,20 @@ int launch_head16(int dtype, const uint16_t* Hm, const uint16_t* W,
 // vocabulary slabs per row (pmax/psum/parg columns) the head launch for this
 // layout and live-row bound writes; at most ceil(V / 128)
 int head16_slabs(int vocab, int tiled = 0, int live_bound = 1);
-int launch_gemm_f32(int epi, const float* A, const float* B, const float* B2,
-                    float* C, int M, int N, int K, int ldc, int cls,
-                    const int32_t* m_count, hipStream_t s);
+// fp32 products (gemm_f32.hip): the norm of the A rows (gain may be null), the
+// rotary embedding and the gather of the masked rows are part of them
+int launch_f32_qkv(const float* X, const float* gain, float eps, const float* W,
+                   float* QKV, int rows, int d, int head_dim,
+                   const int32_t* pos, const float* cs, const SeqPack& sp,
+                   hipStream_t s);
+int launch_f32_swiglu(const float* X, const float* gain, float eps,
+                      const float* Wg, const float* Wu, float* H, int rows,
+                      int d, int ffn, const SeqPack& sp, hipStream_t s);
+int launch_f32_add(const float* A, const float* W, float* X, int rows, int d,
+                   int K, const SeqPack& sp, hipStream_t s);
+int launch_f32_head(const float* X, const int32_t* list, const float* gain,
+                    float eps, const float* W, float* logits, int max_rows,
+                    int vocab, int d, const SeqPack& sp, hipStream_t s);
 
 // Attention over the packed batch: qkv [total, 3d] -> o [total, d]
 // Key-range split of the 16-bit attention: a query tile's keys may be

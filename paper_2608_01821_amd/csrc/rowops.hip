@@ -169,7 +169,8 @@ __device__ __forceinline__ void build_row_list(const RowList& rl,
   }
 }
 
-// X[row] = [view | E[prompt] | E[resp or mask]] row; A[row] = RMSNorm(X[row]).
+// X[row] = [view | E[prompt] | E[resp or mask]] row; A[row] = RMSNorm(X[row])
+// where A is given (the fp32 products norm their rows themselves).
 // One extra workgroup after the rows builds the masked-row list meanwhile.
 template <typename Fmt, typename T = typename Fmt::st>
 __global__ void __launch_bounds__(kThreads)
@@ -216,7 +217,7 @@ assemble_norm_kernel(SeqPack sp, ViewPtrs vp, const T* __restrict__ embed,
       for (int i = 0; i < 8; ++i) ss += x[n][i] * x[n][i];
     }
   }
-  norm_store<Fmt>(x, ss, d, gain, eps, A + (size_t)row * d, red);
+  if (A) norm_store<Fmt>(x, ss, d, gain, eps, A + (size_t)row * d, red);
 }
 
 template <typename Fmt, typename T = typename Fmt::st>
@@ -251,31 +252,6 @@ __global__ void rope_table_kernel(int max_pos, int head_dim, double theta,
   const double inv = pow(theta, -(2.0 * i) / (double)head_dim);
   const double a = (double)pos * inv;
   cs[idx] = make_float2((float)cos(a), (float)sin(a));
-}
-
-// In-place rotary embedding of the query and key parts of qkv [rows, 3d]:
-// dim i pairs with dim i + D/2 inside each head (rotate-half form).
-template <typename Fmt, typename T = typename Fmt::st>
-__global__ void __launch_bounds__(kThreads)
-rope_kernel(T* __restrict__ qkv, SeqPack sp, int n_heads, int head_dim,
-            const float2* __restrict__ cs) {
-  const int row = blockIdx.x;
-  const int s = find_seq(sp, row);
-  const int pos = row - sp.row0[s];
-  const int d = n_heads * head_dim;
-  const int half = head_dim / 2;
-  T* base = qkv + (size_t)row * 3 * d;
-  // 2 * n_heads * half pairs: queries then keys
-  for (int p = threadIdx.x; p < 2 * n_heads * half; p += kThreads) {
-    const int which = p / (n_heads * half);
-    const int h = (p / half) % n_heads;
-    const int i = p % half;
-    T* x = base + which * d + h * head_dim;
-    const float2 c = cs[(size_t)pos * half + i];
-    const float a = Fmt::load(x[i]), b = Fmt::load(x[i + half]);
-    x[i] = Fmt::store(a * c.x - b * c.y);
-    x[i + half] = Fmt::store(b * c.x + a * c.y);
-  }
 }
 
 // Hm[j] = RMSNorm_final(X[packed row of masked position list[1+j]]).
@@ -705,8 +681,7 @@ int launch_rmsnorm(const float* X, int rows, int d, const float* gain,
   hipLaunchKernelGGL(rmsnorm_kernel<F>, dim3(rows), dim3(kThreads), 0, s, X, \
                      d, gain, eps, (F::st*)A)
   if (dtype == DAVET_BF16) RMS(BF16S);
-  else if (dtype == DAVET_F16) RMS(F16S);
-  else RMS(F32S);
+  else RMS(F16S);
 #undef RMS
   DAVET_HIP(hipGetLastError());
   return DAVET_OK;
@@ -722,20 +697,6 @@ int launch_rope_table(int max_pos, int head_dim, float theta, float* cs,
   return DAVET_OK;
 }
 
-int launch_rope(void* qkv, int rows, int n_heads, int head_dim, int dtype,
-                const SeqPack& sp, const float* cs, hipStream_t s) {
-  ProfScope ps(KC_ROPE, s);
-#define ROPE(F)                                                             \
-  hipLaunchKernelGGL(rope_kernel<F>, dim3(rows), dim3(kThreads), 0, s,        \
-                     (F::st*)qkv, sp, n_heads, head_dim, (const float2*)cs)
-  if (dtype == DAVET_BF16) ROPE(BF16S);
-  else if (dtype == DAVET_F16) ROPE(F16S);
-  else ROPE(F32S);
-#undef ROPE
-  DAVET_HIP(hipGetLastError());
-  return DAVET_OK;
-}
-
 int launch_final_norm_gather(const float* X, const SeqPack& sp,
                              const int32_t* list, int max_rows, int d,
                              const float* gain, float eps, int dtype, void* Hm,
@@ -746,8 +707,7 @@ int launch_final_norm_gather(const float* X, const SeqPack& sp,
                      dim3(kThreads), 0, s, X, sp, list, d, gain, eps,         \
                      (F::st*)Hm)
   if (dtype == DAVET_BF16) FNG(BF16S);
-  else if (dtype == DAVET_F16) FNG(F16S);
-  else FNG(F32S);
+  else FNG(F16S);
 #undef FNG
   DAVET_HIP(hipGetLastError());
   return DAVET_OK;

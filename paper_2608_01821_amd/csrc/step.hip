@@ -317,8 +317,8 @@ int davet::denoise_step_impl(const davet_model_cfg* cfg, const davet_weights* w,
   const RowList rl{n_seqs * L, list,     conf_out,      argmax_out,
                    slot,       overflow, clear_overflow};
   RUN(launch_assemble_norm(sp, vp, c.dtype, w->embed, prompt_ids, resp_ids,
-                           resp_masked, c.mask_id, c.vocab, d, g0, c.rms_eps, X, A,
-                           pos, rl, s));
+                           resp_masked, c.mask_id, c.vocab, d, g0, c.rms_eps, X,
+                           bf ? A : nullptr, pos, rl, s));
   const int T = sp.total;
   const GemmPlan p_qkv = plan_gemm16(T, 3 * d, d), p_o = plan_gemm16(T, d, d);
   const GemmPlan p_gu = plan_gemm16(T, 2 * F, d), p_dn = plan_gemm16(T, d, F);
@@ -326,9 +326,9 @@ int davet::denoise_step_impl(const davet_model_cfg* cfg, const davet_weights* w,
   bool hm_ready = false;     // Hm holds the final norm of the masked rows
   for (int l = 0; l < c.n_layers; ++l) {
     const davet_layer_weights& lw = w->layers[l];
-    if (!a_ready) RUN(launch_rmsnorm(X, T, d, lw.attn_norm, c.rms_eps,
-                                     c.dtype, A, s));
     if (bf) {
+      if (!a_ready) RUN(launch_rmsnorm(X, T, d, lw.attn_norm, c.rms_eps,
+                                       c.dtype, A, s));
       const uint16_t* Ah = (const uint16_t*)A;
       // QKV projection, rotary embedding on the query and key columns
       RUN(launch_gemm16(dt, EPI_STORE, p_qkv, Ah, (const uint16_t*)lw.wqkv,
@@ -374,24 +374,19 @@ int davet::denoise_step_impl(const davet_model_cfg* cfg, const davet_weights* w,
         }
       }
     } else {
-      RUN(launch_gemm_f32(EPI_STORE, (const float*)A, (const float*)lw.wqkv,
-                          nullptr, (float*)QKV, sp.total, 3 * d, d, 3 * d,
-                          KC_GEMM_F32, nullptr, s));
-      RUN(launch_rope(QKV, sp.total, c.n_heads, c.head_dim, c.dtype, sp, rope, s));
+      // the norms, the rotary embedding and (below) the gather of the masked
+      // rows are part of the products
+      RUN(launch_f32_qkv(X, lw.attn_norm, c.rms_eps, (const float*)lw.wqkv,
+                         (float*)QKV, T, d, c.head_dim, pos, rope, sp, s));
       RUN(launch_attention_f32((const float*)QKV, (float*)O, sp, c.n_heads,
                                c.head_dim, s));
-      RUN(launch_gemm_f32(EPI_ADD_F32, (const float*)O, (const float*)lw.wo,
-                          nullptr, X, sp.total, d, d, d, KC_GEMM_F32, nullptr, s));
-      RUN(launch_rmsnorm(X, sp.total, d, lw.ffn_norm, c.rms_eps, c.dtype, A, s));
-      RUN(launch_gemm_f32(EPI_SWIGLU, (const float*)A, (const float*)lw.wg,
-                          (const float*)lw.wu, (float*)H, sp.total, F, d, F,
-                          KC_GEMM_F32, nullptr, s));
-      RUN(launch_gemm_f32(EPI_ADD_F32, (const float*)H, (const float*)lw.wd,
-                          nullptr, X, sp.total, d, F, d, KC_GEMM_F32, nullptr, s));
-      a_ready = false;
+      RUN(launch_f32_add((const float*)O, (const float*)lw.wo, X, T, d, d, sp, s));
+      RUN(launch_f32_swiglu(X, lw.ffn_norm, c.rms_eps, (const float*)lw.wg,
+                            (const float*)lw.wu, (float*)H, T, d, F, sp, s));
+      RUN(launch_f32_add((const float*)H, (const float*)lw.wd, X, T, d, F, sp, s));
     }
   }
-  if (!hm_ready)
+  if (bf && !hm_ready)
     RUN(launch_final_norm_gather(X, sp, list, rows, d, w->final_norm,
                                  c.rms_eps, c.dtype, Hm, s));
   if (bf) {
@@ -408,9 +403,8 @@ int davet::denoise_step_impl(const davet_model_cfg* cfg, const davet_weights* w,
                           argmax_out, s));
   } else {
     float* logits = reinterpret_cast<float*>(ws + lay.logits);
-    RUN(launch_gemm_f32(EPI_STORE, (const float*)Hm, (const float*)w->head,
-                        nullptr, logits, rows, c.vocab, d, c.vocab, KC_HEAD,
-                        list, s));
+    RUN(launch_f32_head(X, list, w->final_norm, c.rms_eps, (const float*)w->head,
+                        logits, rows, c.vocab, d, sp, s));
     RUN(launch_head_reduce_f32(logits, list, rows, c.vocab, c.mask_id,
                                conf_out, argmax_out, logits_out, s));
   }
