@@ -12,10 +12,11 @@
 //
 // Three stages, each a kernel: keys (HBM-bound pass over v: one wavefront
 // per token or grid edge, float64 accumulation), decisions (one 1024-thread
-// workgroup per crop, everything in LDS: a rank per key, then for merge a
-// single-lane union-find over the ranked edges, whose partition snapshots
-// are labelled and scattered by all lanes), and the level rows (CSR means,
-// float64 sums in member order, rounded once).
+// workgroup per crop, everything in LDS: the keys are sorted; prune keeps a
+// prefix; merge finds the minimum spanning tree of the ranked edges and takes
+// components of its first edges, see merge_maps_kernel), and the level rows
+// of every level in one launch (CSR means, float64 sums in member order,
+// rounded once).
 
 #include <mutex>
 #include <string>
@@ -103,6 +104,138 @@ __device__ int block_scan_excl(int x, int* sh, int* total) {
   return r;
 }
 
+// Bitonic sort of S * RZ_NT elements by the whole block, in registers: element
+// q * RZ_NT + tid is slot q of thread tid.  A partner at distance j < 64 is a
+// lane of the same wave (shuffles), at 64 <= j < RZ_NT a thread of another
+// wave (through LDS, two barriers: 10 of the 55 stages of 1024 elements), at
+// j >= RZ_NT another slot.  E: element type with shuffle(j), put(i) / get(i)
+// (LDS exchange) and before(other), a strict order.  A sort with the elements
+// in LDS spent 0.36 us on each stage, mostly LDS latency.
+template <int S, typename E>
+__device__ __forceinline__ void bitonic_sort(E (&x)[S]) {
+  const int tid = threadIdx.x;
+  // slot q against partner p: keeps the earlier element if `first`
+  auto keep = [](E& mine, const E& other, bool first) {
+    if (first != mine.before(other)) mine = other;
+  };
+  for (int k = 2; k <= S * RZ_NT; k <<= 1) {
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      if (j >= RZ_NT) {
+#pragma unroll
+        for (int dj = S / 2; dj > 0; dj >>= 1) {
+          if (j != dj * RZ_NT) continue;
+#pragma unroll
+          for (int q = 0; q < S; ++q) {
+            if (q & dj) continue;
+            const bool asc = ((q * RZ_NT + tid) & k) == 0;
+            const E lo = x[q], hi = x[q | dj];
+            keep(x[q], hi, asc);
+            keep(x[q | dj], lo, !asc);
+          }
+        }
+      } else if (j >= 64) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < S; ++q) x[q].put(q * RZ_NT + tid);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+          const int i = q * RZ_NT + tid;
+          keep(x[q], x[q].get(i ^ j), ((i & j) == 0) == ((i & k) == 0));
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+          const int i = q * RZ_NT + tid;
+          keep(x[q], x[q].shuffle(j), ((i & j) == 0) == ((i & k) == 0));
+        }
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// A key of the crop: its code and index (padding: code 0, below the code of
+// any key, and an index past the last).
+struct KeyElem {
+  uint64_t code;
+  int id;
+  uint64_t* lds_code;
+  uint16_t* lds_id;
+  __device__ __forceinline__ bool before(const KeyElem& o) const {
+    return code > o.code || (code == o.code && id < o.id);
+  }
+  __device__ __forceinline__ KeyElem shuffle(int j) const {
+    KeyElem e = *this;
+    e.code = ((uint64_t)__shfl_xor((uint32_t)(code >> 32), j, 64) << 32) |
+             __shfl_xor((uint32_t)code, j, 64);
+    e.id = __shfl_xor(id, j, 64);
+    return e;
+  }
+  __device__ __forceinline__ void put(int i) const {
+    lds_code[i] = code;
+    lds_id[i] = (uint16_t)id;
+  }
+  __device__ __forceinline__ KeyElem get(int i) const {
+    KeyElem e = *this;
+    e.code = lds_code[i];
+    e.id = lds_id[i];
+    return e;
+  }
+};
+
+// A number (ascending).
+struct U32Elem {
+  uint32_t v;
+  uint32_t* lds;
+  __device__ __forceinline__ bool before(const U32Elem& o) const { return v < o.v; }
+  __device__ __forceinline__ U32Elem shuffle(int j) const {
+    return U32Elem{__shfl_xor(v, j, 64), lds};
+  }
+  __device__ __forceinline__ void put(int i) const { lds[i] = v; }
+  __device__ __forceinline__ U32Elem get(int i) const { return U32Elem{lds[i], lds}; }
+};
+
+// Sorts the n <= S * RZ_NT keys of a crop: order[r] = index of the key taken
+// r-th.  code and order hold S * RZ_NT entries.
+template <int S>
+__device__ __forceinline__ void sort_keys_s(const double* __restrict__ keys,
+                                            int n, uint64_t* code,
+                                            uint16_t* order) {
+  KeyElem x[S];
+#pragma unroll
+  for (int q = 0; q < S; ++q) {
+    const int i = q * RZ_NT + threadIdx.x;
+    x[q] = KeyElem{i < n ? key_code(keys[i]) : 0ull, i, code, order};
+  }
+  bitonic_sort<S>(x);
+#pragma unroll
+  for (int q = 0; q < S; ++q) order[q * RZ_NT + threadIdx.x] = (uint16_t)x[q].id;
+  __syncthreads();
+}
+
+template <int MAX_S>
+__device__ __forceinline__ void sort_keys(const double* __restrict__ keys, int n,
+                                          uint64_t* code, uint16_t* order) {
+  if (n <= RZ_NT) sort_keys_s<1>(keys, n, code, order);
+  else if (n <= 2 * RZ_NT) sort_keys_s<2>(keys, n, code, order);
+  else if (MAX_S == 4 || n <= 4 * RZ_NT) sort_keys_s<4>(keys, n, code, order);
+  else sort_keys_s<MAX_S>(keys, n, code, order);
+}
+
+// out[i] = the i-th smallest of the n <= S * RZ_NT values of x (padding:
+// 0xffffffff), in LDS of S * RZ_NT entries; x is read first.
+template <int S>
+__device__ __forceinline__ void sort_u32(uint32_t* x) {
+  U32Elem e[S];
+#pragma unroll
+  for (int q = 0; q < S; ++q) e[q] = U32Elem{x[q * RZ_NT + threadIdx.x], x};
+  bitonic_sort<S>(e);
+#pragma unroll
+  for (int q = 0; q < S; ++q) x[q * RZ_NT + threadIdx.x] = e[q].v;
+  __syncthreads();
+}
+
 // ------------------------------------------------------------------ keys --
 
 // L1 norm of every token: one wavefront per token.
@@ -182,23 +315,20 @@ __device__ void identity_map(const MapPtrs& mp, int K, int n_crops, int N) {
     mp.offs[K - 1][n_crops * N] = n_crops * N;
 }
 
-// Prune: rank every token of the crop by its key, then per level keep the
-// tokens ranked below n_l, compacted in index order by a block scan.
+// Prune: sort the crop's tokens by key, then per level keep the tokens ranked
+// below n_l, compacted in index order by a block scan.  Latency-bound, one
+// workgroup per crop, mostly the sort: 15 us for five 27 x 27 crops (29 while
+// each thread ranked its token against all others).
 __global__ void __launch_bounds__(RZ_NT)
 prune_maps_kernel(const double* __restrict__ keys, int n_crops, int G, int K,
                   LvlCnt cnt, MapPtrs mp) {
   __shared__ uint64_t code[RZ_MAXN];
-  __shared__ int rank[RZ_MAXN];
+  __shared__ uint16_t order[RZ_MAXN];
+  __shared__ uint16_t rank[RZ_MAXN];
   __shared__ int sh[RZ_NT / 64 + 1];
   const int N = G * G, c = blockIdx.x, tid = threadIdx.x;
-  for (int i = tid; i < N; i += RZ_NT) code[i] = key_code(keys[(size_t)c * N + i]);
-  __syncthreads();
-  for (int i = tid; i < N; i += RZ_NT) {
-    const uint64_t ki = code[i];
-    int r = 0;
-    for (int j = 0; j < N; ++j) r += before(code[j], j, ki, i);
-    rank[i] = r;
-  }
+  sort_keys<4>(keys + (size_t)c * N, N, code, order);
+  for (int r = tid; r < N; r += RZ_NT) rank[order[r]] = (uint16_t)r;
   __syncthreads();
   for (int l = 0; l < K - 1; ++l) {
     const int n = cnt.n[l];
@@ -224,67 +354,141 @@ prune_maps_kernel(const double* __restrict__ keys, int n_crops, int G, int K,
   identity_map(mp, K, n_crops, N);
 }
 
-// root of x with path halving (single writer)
-__device__ __forceinline__ int find_halve(int* parent, int x) {
-  while (parent[x] != x) {
-    const int gp = parent[parent[x]];
-    parent[x] = gp;
-    x = gp;
+// parent[] becomes root[] (every chain of the forest shortcut): pointer
+// doubling, in place; a thread may read an entry another has already
+// shortened, which is an ancestor all the same.
+__device__ __forceinline__ void flatten(int* parent, int N) {
+  bool more = true;
+  while (__syncthreads_or(more)) {
+    more = false;
+    for (int i = threadIdx.x; i < N; i += RZ_NT) {
+      const int p = parent[i], q = parent[p];
+      if (p != q) {
+        parent[i] = q;
+        more = true;
+      }
+    }
   }
-  return x;
 }
 
-// Merge: rank the crop's edges by key; lane 0 of the block runs the
-// union-find over the ranked edges (the larger root joins the smaller, so a
-// root is its group's smallest member) until n_l groups remain; then all
-// lanes label every token with its root, count group sizes, scan sizes and
-// roots in index order (member start and group index), and scatter members.
+// Merge.  Taking the edges in key order and joining groups (Kruskal) keeps
+// exactly the edges of the minimum spanning tree of the ranks, which the
+// strict order makes unique, and after N - n joins n groups are left: the
+// components of the tree's first N - n edges in rank order.  So the block
+// sorts the edges, finds the tree by Boruvka rounds (every component takes
+// its lowest-ranked outgoing edge: LDS atomic minima, at most log2 N rounds),
+// numbers the tree's edges by rank with a prefix sum, and per level joins the
+// ends of the first N - n_l of them (the larger label joins the smaller, so
+// a label ends as its group's smallest member), counts group sizes, scans
+// sizes and roots in index order (member start and group index) and lists the
+// members by a sort of (label, token).  Latency-bound, one workgroup per
+// crop: 80 us for four 27 x 27 crops (457 with the joins in a single lane).
 __global__ void __launch_bounds__(RZ_NT)
 merge_maps_kernel(const double* __restrict__ keys, int n_crops, int G, int K,
                   LvlCnt cnt, MapPtrs mp) {
-  __shared__ uint64_t code[RZ_MAXE];
-  __shared__ uint16_t order[RZ_MAXE];
+  constexpr int P_E = 2 * RZ_MAXN;                 // >= RZ_MAXE, power of two
+  static_assert(P_E >= RZ_MAXE && RZ_MAXE % 2 == 0, "edge arrays");
+  // code: the sort's keys, afterwards the rounds' minima and the member sort
+  __shared__ uint64_t code[P_E];
+  __shared__ uint16_t order[P_E];      // edges by rank
+  __shared__ uint16_t tree[P_E];       // per rank: in the tree; then its number
   __shared__ int parent[RZ_MAXN];
   __shared__ int label[RZ_MAXN];
-  __shared__ int aux[RZ_MAXN];          // group sizes, then member starts
   __shared__ int sh[RZ_NT / 64 + 1];
-  __shared__ int s_groups, s_ptr;
   const int N = G * G, E = 2 * G * (G - 1), c = blockIdx.x, tid = threadIdx.x;
-  for (int e = tid; e < E; e += RZ_NT) code[e] = key_code(keys[(size_t)c * E + e]);
-  for (int i = tid; i < N; i += RZ_NT) parent[i] = i;
-  __syncthreads();
-  for (int e = tid; e < E; e += RZ_NT) {
-    const uint64_t ke = code[e];
-    int r = 0;
-    for (int f = 0; f < E; ++f) r += before(code[f], f, ke, e);
-    order[r] = (uint16_t)e;
+  sort_keys<8>(keys + (size_t)c * E, E, code, order);
+  uint32_t* best = reinterpret_cast<uint32_t*>(code);       // [N]
+  uint32_t* msort = best + RZ_MAXN;                         // [RZ_MAXN]
+  uint32_t* ends = msort + RZ_MAXN;                         // [P_E] by rank
+  constexpr uint32_t NONE = 0xffffffffu;
+  for (int r = tid; r < E; r += RZ_NT) {
+    int a, b;
+    edge_ends(order[r], G, a, b);
+    ends[r] = (uint32_t)a | ((uint32_t)b << 16);
+    tree[r] = 0;
   }
-  if (tid == 0) { s_groups = N; s_ptr = 0; }
+  for (int i = tid; i < N; i += RZ_NT) {
+    label[i] = i;
+    best[i] = NONE;
+  }
+  __syncthreads();
+  // ---- the spanning tree
+  for (;;) {
+    bool open = false;
+    for (int r = tid; r < E; r += RZ_NT) {
+      const uint32_t ab = ends[r];
+      const int la = label[ab & 0xffffu], lb = label[ab >> 16];
+      if (la != lb) {
+        atomicMin(&best[la], (uint32_t)r);
+        atomicMin(&best[lb], (uint32_t)r);
+        open = true;
+      }
+    }
+    // every round joins every remaining group to another: at most 12 rounds
+    if (!__syncthreads_or(open)) break;
+    for (int i = tid; i < N; i += RZ_NT) {
+      int p = i;
+      if (label[i] == i && best[i] != NONE) {
+        const uint32_t r = best[i];
+        const uint32_t ab = ends[r];
+        const int la = label[ab & 0xffffu], lb = label[ab >> 16];
+        p = la == i ? lb : la;
+        // two groups that took the same edge: the smaller stays the root
+        if (best[p] == r && i < p) p = i;
+        tree[r] = 1;
+      }
+      parent[i] = p;
+    }
+    flatten(parent, N);
+    for (int i = tid; i < N; i += RZ_NT) {
+      label[i] = parent[label[i]];
+      best[i] = NONE;
+    }
+    __syncthreads();
+  }
+  // ---- number the tree's edges by rank (0, 1, ...; others 0xffff)
+  {
+    constexpr int PER = P_E / RZ_NT;
+    uint16_t in[PER];
+    int local = 0, total;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int r = tid * PER + q;
+      in[q] = r < E ? tree[r] : 0;
+      local += in[q];
+    }
+    int k = block_scan_excl(local, sh, &total);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int r = tid * PER + q;
+      if (r < E) tree[r] = in[q] ? (uint16_t)k++ : (uint16_t)0xffff;
+    }
+  }
+  for (int i = tid; i < N; i += RZ_NT) label[i] = i;
   __syncthreads();
   for (int l = K - 2; l >= 0; --l) {
     const int n = cnt.n[l];
-    if (tid == 0) {
-      int groups = s_groups, p = s_ptr;
-      // the grid graph is connected, so groups reaches n before p reaches E
-      while (groups > n && p < E) {
-        int a, b;
-        edge_ends(order[p++], G, a, b);
-        const int ra = find_halve(parent, a), rb = find_halve(parent, b);
-        if (ra != rb) {
-          parent[max(ra, rb)] = min(ra, rb);
-          --groups;
+    // ---- join the ends of the first N - n tree edges
+    for (;;) {
+      bool open = false;
+      for (int r = tid; r < E; r += RZ_NT) {
+        if ((int)tree[r] >= N - n) continue;
+        const uint32_t ab = ends[r];
+        const int la = label[ab & 0xffffu], lb = label[ab >> 16];
+        if (la != lb) {
+          // roots only: label[] is flat here, and a root joins a smaller one
+          atomicMin(&label[max(la, lb)], min(la, lb));
+          open = true;
         }
       }
-      s_groups = groups;
-      s_ptr = p;
+      if (!__syncthreads_or(open)) break;
+      flatten(label, N);
     }
-    __syncthreads();
-    for (int i = tid; i < N; i += RZ_NT) {
-      int x = i;
-      while (parent[x] != x) x = parent[x];
-      label[i] = x;
-      aux[i] = 0;
-    }
+    // ---- sizes, member starts, group indices
+    int* aux = parent;
+    for (int i = tid; i < N; i += RZ_NT) aux[i] = 0;
+    for (int i = tid; i < RZ_MAXN; i += RZ_NT)
+      msort[i] = i < N ? ((uint32_t)label[i] << 13) | (uint32_t)i : NONE;
     __syncthreads();
     for (int i = tid; i < N; i += RZ_NT) atomicAdd(&aux[label[i]], 1);
     __syncthreads();
@@ -302,9 +506,6 @@ merge_maps_kernel(const double* __restrict__ keys, int n_crops, int G, int K,
     int g = block_scan_excl(lrt, sh, &total);
 #pragma unroll
     for (int q = 0; q < RZ_PER; ++q) {
-      const int i = tid * RZ_PER + q;
-      if (i >= N) continue;
-      aux[i] = start;                     // this thread's own entries only
       if (rt[q]) {
         // g < n always (exactly n roots remain); the test keeps a broken
         // invariant from writing past the level's offsets
@@ -313,14 +514,13 @@ merge_maps_kernel(const double* __restrict__ keys, int n_crops, int G, int K,
       }
       start += sz[q];
     }
-    __syncthreads();
+    // ---- members: groups by label (their smallest member), tokens ascending
     if (mp.mem[l]) {
-      for (int i = tid; i < N; i += RZ_NT) {
-        const int r = label[i];
-        int pos = 0;
-        for (int j = r; j < i; ++j) pos += (label[j] == r) ? 1 : 0;
-        mp.mem[l][c * N + aux[r] + pos] = c * N + i;
-      }
+      if (N <= RZ_NT) sort_u32<1>(msort);
+      else if (N <= 2 * RZ_NT) sort_u32<2>(msort);
+      else sort_u32<4>(msort);
+      for (int i = tid; i < N; i += RZ_NT)
+        mp.mem[l][c * N + i] = c * N + (int)(msort[i] & 0x1fffu);
     }
     if (c == 0 && tid == 0 && mp.offs[l]) mp.offs[l][n_crops * n] = n_crops * N;
     __syncthreads();
@@ -330,74 +530,131 @@ merge_maps_kernel(const double* __restrict__ keys, int n_crops, int G, int K,
 
 // ----------------------------------------------------------------- levels --
 
-// Token t = float64 sum of rows mem[offs[t] .. offs[t+1]) of v in that
-// order, divided by the member count, rounded once.  Eight features per
-// thread; the rows of eight members are loaded together (independent loads
-// in flight) and then added one member after another, so large merged
-// groups are not bound by one load latency per member.
+// Level rows of every level below the finest, one launch for all levels
+// (block x: a token of level 0, then of level 1, ...: the coarsest level's
+// groups are the largest and start first).
+struct CsrLevels {
+  const int32_t* offs[DAVET_MAX_LEVELS];
+  const int32_t* mem[DAVET_MAX_LEVELS];
+  void* out[DAVET_MAX_LEVELS];
+  int n[DAVET_MAX_LEVELS];
+};
+
+// Prune: token t is row mem[t] of v, copied (16 bytes a thread; row_bytes is
+// a multiple of 16).
+__global__ void __launch_bounds__(256)
+copy_rows_kernel(const char* __restrict__ v, CsrLevels lv, int row_bytes) {
+  int l = 0, t = blockIdx.x;
+  while (t >= lv.n[l]) t -= lv.n[l++];
+  const int e0 = (blockIdx.y * 256 + threadIdx.x) * 16;
+  if (e0 >= row_bytes) return;
+  *reinterpret_cast<u32x4*>(static_cast<char*>(lv.out[l]) + (size_t)t * row_bytes +
+                            e0) =
+      *reinterpret_cast<const u32x4*>(v + (size_t)lv.mem[l][t] * row_bytes + e0);
+}
+
+// Merge: token t = float64 sum of rows mem[offs[t] .. offs[t+1]) of v in that
+// order, divided by the member count, rounded once.  The largest merged
+// groups hold most of a crop, so the time is their chain of member rows: a
+// block owns 512 features of a token, stages the member ids in LDS and keeps
+// up to 2 x BATCH rows in flight.
+//
+// fp16 (EXACT): a finite fp16 value is a multiple of 2^-24 below 2^16, so a
+// float64 sum of up to 4096 of them is exact in any order; the block's four
+// waves take every fourth member of all 512 features (16-byte loads) and add
+// their sums in LDS.  bf16 and fp32 sums depend on the order, so there every
+// thread adds all members of its 2 features one after another.
+// Four 27 x 27 fp16 crops, both levels: 30 us (329 with all members in one
+// chain of 8 rows in flight, ids loaded with each batch, a launch per level).
+constexpr int CSR_IDS = 512;                       // member ids staged at once
+static_assert(RZ_MAXN <= 4096, "exact fp16 sums");
+
 template <typename Fmt>
 __global__ void __launch_bounds__(256)
-pool_csr_kernel(const typename Fmt::st* __restrict__ v,
-                const int32_t* __restrict__ offs,
-                const int32_t* __restrict__ mem, int d,
-                typename Fmt::st* __restrict__ out) {
+pool_csr_kernel(const typename Fmt::st* __restrict__ v, CsrLevels lv, int d) {
   using T = typename Fmt::st;
-  constexpr int B = 8;                            // members per batch
-  constexpr int Q = sizeof(T) == 2 ? 1 : 2;       // 16-byte pieces per row
-  const int t = blockIdx.x;
-  const int e0 = (blockIdx.y * 256 + threadIdx.x) * 8;
-  if (e0 >= d) return;
-  const int b = offs[t], e = offs[t + 1];
-  double acc[8];
+  constexpr bool EXACT = Fmt::dtype == DAVET_F16;
+  constexpr int VEC = EXACT ? 8 : 2;               // features per thread
+  constexpr int STEP = EXACT ? 4 : 1;              // waves per feature
+  constexpr int BATCH = EXACT ? 8 : 32;
+  constexpr int W = VEC * (int)sizeof(T) / 4;      // 32-bit words per row piece
+  typedef uint32_t words __attribute__((ext_vector_type(W),
+                                        aligned(W >= 4 ? 16 : W * 4)));
+  __shared__ int32_t ids[CSR_IDS];
+  __shared__ double part[EXACT ? 3 : 1][EXACT ? VEC : 1][64];
+  int l = 0, t = blockIdx.x;
+  while (t >= lv.n[l]) t -= lv.n[l++];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int e0 = blockIdx.y * 512 + (EXACT ? lane : threadIdx.x) * VEC;
+  const bool live = e0 < d;                        // d is a multiple of 8
+  const T* src = v + (live ? e0 : 0);
+  const int32_t* mem = lv.mem[l];
+  const int b = lv.offs[l][t], e = lv.offs[l][t + 1];
+  double acc[VEC];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) acc[k] = 0.0;
-  for (int m0 = b; m0 < e; m0 += B) {
-    const int nb = min(B, e - m0);
-    u32x4 raw[B][Q];
+  for (int k = 0; k < VEC; ++k) acc[k] = 0.0;
+  for (int c0 = b; c0 < e; c0 += CSR_IDS) {
+    const int nc = min(CSR_IDS, e - c0);
+    if (c0 != b) __syncthreads();
+    for (int i = threadIdx.x; i < nc; i += 256) ids[i] = mem[c0 + i];
+    __syncthreads();
+    const int first = EXACT ? wave : 0;
+    words cur[BATCH], nxt[BATCH];
+    // members i0, i0 + STEP, ... of the staged ones (the last one repeated)
+    auto load = [&](int i0, words (&r)[BATCH]) {
 #pragma unroll
-    for (int k = 0; k < B; ++k) {
-      if (k < nb) {
-        const T* p = v + (size_t)mem[m0 + k] * d + e0;
+      for (int k = 0; k < BATCH; ++k)
+        r[k] = *reinterpret_cast<const words*>(
+            src + (size_t)ids[min(i0 + k * STEP, nc - 1)] * d);
+    };
+    if (first < nc) load(first, cur);
+    for (int i0 = first; i0 < nc; i0 += BATCH * STEP) {
+      if (i0 + BATCH * STEP < nc) load(i0 + BATCH * STEP, nxt);
 #pragma unroll
-        for (int q = 0; q < Q; ++q)
-          raw[k][q] = *reinterpret_cast<const u32x4*>(p + q * (8 / Q));
-      }
-    }
+      for (int k = 0; k < BATCH; ++k) {
+        if (i0 + k * STEP < nc) {
 #pragma unroll
-    for (int k = 0; k < B; ++k) {
-      if (k < nb) {
-        if constexpr (sizeof(T) == 2) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            acc[2 * q] += (double)Fmt::load((uint16_t)(raw[k][0][q] & 0xffffu));
-            acc[2 * q + 1] += (double)Fmt::load((uint16_t)(raw[k][0][q] >> 16));
+          for (int q = 0; q < W; ++q) {
+            if constexpr (sizeof(T) == 2) {
+              acc[2 * q] += (double)Fmt::load((uint16_t)(cur[k][q] & 0xffffu));
+              acc[2 * q + 1] += (double)Fmt::load((uint16_t)(cur[k][q] >> 16));
+            } else {
+              acc[q] += (double)__uint_as_float(cur[k][q]);
+            }
           }
-        } else {
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            acc[j] += (double)__uint_as_float(raw[k][j / 4][j % 4]);
         }
       }
+#pragma unroll
+      for (int k = 0; k < BATCH; ++k) cur[k] = nxt[k];
     }
   }
-  const double cnt = (double)(e - b);
-  typename Fmt::st* dst = out + (size_t)t * d + e0;
-  if constexpr (sizeof(typename Fmt::st) == 2) {
-    u32x4 w;
+  if constexpr (EXACT) {
+    if (e - b > 1) {                               // the same for the block
+      if (wave > 0)
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+        for (int k = 0; k < VEC; ++k) part[wave - 1][k][lane] = acc[k];
+      __syncthreads();
+      if (wave == 0)
+#pragma unroll
+        for (int w = 0; w < 3; ++w)
+#pragma unroll
+          for (int k = 0; k < VEC; ++k) acc[k] += part[w][k][lane];
+    }
+    if (wave > 0) return;
+  }
+  if (!live) return;
+  const double cnt = (double)(e - b);
+  words w;
+#pragma unroll
+  for (int q = 0; q < W; ++q) {
+    if constexpr (sizeof(T) == 2)
       w[q] = (uint32_t)Fmt::from_f64(acc[2 * q] / cnt) |
              ((uint32_t)Fmt::from_f64(acc[2 * q + 1] / cnt) << 16);
-    *reinterpret_cast<u32x4*>(dst) = w;
-  } else {
-    float4 a, bq;
-    a.x = (float)(acc[0] / cnt); a.y = (float)(acc[1] / cnt);
-    a.z = (float)(acc[2] / cnt); a.w = (float)(acc[3] / cnt);
-    bq.x = (float)(acc[4] / cnt); bq.y = (float)(acc[5] / cnt);
-    bq.z = (float)(acc[6] / cnt); bq.w = (float)(acc[7] / cnt);
-    *reinterpret_cast<float4*>(dst) = a;
-    *reinterpret_cast<float4*>(dst + 4) = bq;
+    else
+      w[q] = __float_as_uint((float)(acc[q] / cnt));
   }
+  *reinterpret_cast<words*>(reinterpret_cast<T*>(lv.out[l]) + (size_t)t * d + e0) = w;
 }
 
 // ------------------------------------------------------------------ host --
@@ -481,12 +738,11 @@ int launch_maps(const davet_view_geom& g, const double* keys, const MapPtrs& mp,
 }
 
 template <typename Fmt>
-void launch_pool_csr_t(const void* v, const int32_t* offs, const int32_t* mem,
-                       int n_tok, int d, void* out, hipStream_t s) {
-  dim3 grid(n_tok, (d / 8 + 255) / 256);
-  hipLaunchKernelGGL(pool_csr_kernel<Fmt>, grid, dim3(256), 0, s,
-                     reinterpret_cast<const typename Fmt::st*>(v), offs, mem, d,
-                     reinterpret_cast<typename Fmt::st*>(out));
+void launch_pool_csr_t(const void* v, const CsrLevels& lv, int n_tok, int d,
+                       hipStream_t s) {
+  hipLaunchKernelGGL(pool_csr_kernel<Fmt>, dim3(n_tok, (d + 511) / 512),
+                     dim3(256), 0, s,
+                     reinterpret_cast<const typename Fmt::st*>(v), lv, d);
 }
 
 // Scratch layout: keys, then (offsets, members) of each level < K-1, each
@@ -547,14 +803,26 @@ int build_views_realizer(const davet_view_geom& g, const void* v,
   if (rc) return rc;
   const LvlCnt lc = level_counts(g);
   ProfScope ps(KC_VIEWS, s);
+  CsrLevels lv{};
+  int n_tok = 0;
   for (int l = 0; l + 1 < g.K; ++l) {
-    const int n = g.n_crops * lc.n[l];
-    if (g.dtype == DAVET_BF16)
-      launch_pool_csr_t<BF16S>(v, mp.offs[l], mp.mem[l], n, g.d, levels[l], s);
-    else if (g.dtype == DAVET_F16)
-      launch_pool_csr_t<F16S>(v, mp.offs[l], mp.mem[l], n, g.d, levels[l], s);
-    else
-      launch_pool_csr_t<F32S>(v, mp.offs[l], mp.mem[l], n, g.d, levels[l], s);
+    lv.offs[l] = mp.offs[l];
+    lv.mem[l] = mp.mem[l];
+    lv.out[l] = levels[l];
+    lv.n[l] = g.n_crops * lc.n[l];
+    n_tok += lv.n[l];
+  }
+  if (n_tok == 0) return DAVET_OK;               // K = 1
+  if (g.realizer == DAVET_REALIZER_PRUNE) {
+    const int row_bytes = g.d * (int)dtype_size(g.dtype);
+    hipLaunchKernelGGL(copy_rows_kernel, dim3(n_tok, (row_bytes + 4095) / 4096),
+                       dim3(256), 0, s, static_cast<const char*>(v), lv, row_bytes);
+  } else if (g.dtype == DAVET_BF16) {
+    launch_pool_csr_t<BF16S>(v, lv, n_tok, g.d, s);
+  } else if (g.dtype == DAVET_F16) {
+    launch_pool_csr_t<F16S>(v, lv, n_tok, g.d, s);
+  } else {
+    launch_pool_csr_t<F32S>(v, lv, n_tok, g.d, s);
   }
   DAVET_HIP(hipGetLastError());
   return DAVET_OK;
