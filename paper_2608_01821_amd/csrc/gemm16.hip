@@ -86,6 +86,7 @@ struct EpiArgs {
   int b_tiled;
   // non-finite 16-bit values stored by EPI_STORE / EPI_SWIGLU (may be null)
   int32_t* overflow;
+  int m_band;            // row tiles per band of the tile order
 };
 
 __device__ __forceinline__ int remap_xcd(int bid, int nwg) {
@@ -93,6 +94,22 @@ __device__ __forceinline__ int remap_xcd(int bid, int nwg) {
   if (bid >= full) return bid;
   const int per = full >> 3;
   return (bid & 7) * per + (bid >> 3);
+}
+
+// Order of the tiles: bands of m_band row tiles; in a band row tiles fastest,
+// then K splits, then columns.
+__device__ __forceinline__ void locate_tile(int tile, int n_mtiles,
+                                            int n_ntiles, int ksplit,
+                                            int m_band, int& mb, int& ks,
+                                            int& nb) {
+  const int per_band = m_band * ksplit * n_ntiles;
+  const int band = tile / per_band;
+  const int in_band = tile - band * per_band;
+  const int rows = min(m_band, n_mtiles - band * m_band);
+  mb = band * m_band + in_band % rows;
+  const int rest = in_band / rows;
+  ks = rest % ksplit;
+  nb = rest / ksplit;
 }
 
 template <int N>
@@ -127,6 +144,15 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
 __device__ __forceinline__ void dma16(const void* g, void* lds) {
   __builtin_amdgcn_global_load_lds(g, (lds_ptr_t)lds, 16, 0, 0);
+}
+
+// The same from a wave-uniform address, with `left` bytes behind it (lanes
+// past them read zeros), and a 32-bit offset per lane.
+__device__ __forceinline__ void dma16_from(const char* from, uint32_t left,
+                                           uint32_t off, void* lds) {
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char*>(from), 0, left, 0x00027000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)lds, 16, off, 0, 0, 0);
 }
 
 // Byte offset of chunk c (16 B) of row r inside a stage of BK-wide rows.
@@ -170,10 +196,8 @@ gemm16_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
 
   const int nwg = gridDim.x;
   const int tile = remap_xcd(blockIdx.x, nwg);
-  const int mb = tile % n_mtiles;
-  const int rest = tile / n_mtiles;
-  const int ks = rest % ksplit;
-  const int nb = rest / ksplit;
+  int mb, ks, nb;
+  locate_tile(tile, n_mtiles, n_ntiles, ksplit, ep.m_band, mb, ks, nb);
   int m_live = M;
   if constexpr (EPI == EPI_HEAD) m_live = ep.list[0];
   const int n0 = nb * BN;
@@ -513,16 +537,448 @@ gemm16_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
   }  // M tiles
 }
 
+// Row tiles per band of the tile order.  An XCD works on 32 consecutive tiles
+// at a time: in bands of 8 that is 8 row tiles x 4 columns, 12 operand tiles
+// through its L2 instead of 33; up to 16 row tiles one band is as fast.
+int m_band(int mt) { return mt > 16 ? 8 : mt; }
+
 template <typename Fmt, typename V, int EPI>
 int launch_tiles(const uint16_t* A, const uint16_t* B, const uint16_t* B2,
-                 int M, int N, int K, int ksplit, const EpiArgs& ep,
+                 int M, int N, int K, int ksplit, EpiArgs ep,
                  hipStream_t s, int max_mtiles = 1 << 30) {
   const int mt = std::min((M + V::BM - 1) / V::BM, max_mtiles);
   const int nt = (N + V::BN - 1) / V::BN;
   const int nwg = mt * nt * ksplit;
+  ep.m_band = m_band(mt);
   hipLaunchKernelGGL((gemm16_kernel<Fmt, V, EPI>), dim3(nwg),
                      dim3(64 * V::WAVES), 0, s, A, B, B2, M, N, K, mt, nt,
                      ksplit, ep);
+  DAVET_HIP(hipGetLastError());
+  return DAVET_OK;
+}
+
+// Joins another part (m2, s2, a2) into a row's (max, sum exp, first argmax).
+__device__ __forceinline__ void head_join(float& m, float& s, int& a, float m2,
+                                          float s2, int a2) {
+  const float mm = fmaxf(m, m2);
+  float ns = 0.f;
+  if (m != -INFINITY) ns += s * __expf(m - mm);
+  if (m2 != -INFINITY) ns += s2 * __expf(m2 - mm);
+  a = (m2 > m || (m2 == m && a2 < a)) ? a2 : a;
+  m = mm;
+  s = ns;
+}
+template <int X>
+__device__ __forceinline__ void head_join_lanes(float& m, float& s, int& a) {
+  const float m2 = __shfl_xor(m, X, 64), s2 = __shfl_xor(s, X, 64);
+  const int a2 = __shfl_xor(a, X, 64);
+  head_join(m, s, a, m2, s2, a2);
+}
+// The 256 x 256 tile of 8 wavefronts in a 2 x 4 grid, a wave accumulating
+// 128 x 64, K in slabs of 64.  A slab is worked off in two phases, a 64 x 64
+// half of the wave's block each (32 matrix ops); a phase is a read section
+// (LDS fragments, global->LDS loads of a later slab) and a matrix section,
+// each closed by a barrier.  The waves of row 1 run one section behind those
+// of row 0, and a SIMD holds one of each, so that one wave's reads always sit
+// under the other's matrix ops.
+//
+// LDS: two slabs, each four 128-row half tiles (A0, A1, B0, B1) of 16 KB:
+// half h of A holds rows h*64 .. +63 of both wave rows, half h of B the
+// 16-column blocks 2h, 2h+1 of the four wave columns.  Phase 0 reads A0, B0
+// and B1, phase 1 A1.  A read section ends with its fragments in registers, so
+// from the next phase on both wave rows may load over what it read: slab
+// t+2's A0, B0, B1 in phase 1 of slab t, its A1 in phase 0 of slab t+1, three
+// phases before their first use.  What the next phase reads has landed once at
+// most the eight youngest loads are outstanding.
+//
+// The matrix ops take the weights as their first operand, so a lane holds four
+// consecutive columns of one row per accumulator and stores (and, for the
+// residual, loads) them as one vector.  Column block j of wave column wn is
+// placed where the epilogue wants it (block_col).
+template <int EPI>
+__device__ __forceinline__ int block_col(int wn, int j, bool dual) {
+  if (dual) return (j >> 1) * 128 + wn * 32 + (j & 1) * 16;  // gate | up
+  if (EPI == EPI_STORE)          // dims i and i + 64 of a head in one lane
+    return (wn >> 1) * 128 + (j >> 1) * 64 + (wn & 1) * 32 + (j & 1) * 16;
+  return wn * 64 + j * 16;
+}
+
+template <typename Fmt, int EPI>
+__global__ void __launch_bounds__(512, 1)
+gemm16_phased_kernel(const uint16_t* __restrict__ A,
+                     const uint16_t* __restrict__ B,
+                     const uint16_t* __restrict__ B2, int M, int N, int K,
+                     int n_mtiles, int n_ntiles, int ksplit, EpiArgs ep) {
+  using v8 = typename Fmt::v8;
+  constexpr int HALF = 128 * 64 * 2;           // bytes of a half tile
+  constexpr int SLAB = 4 * HALF;
+  enum { A0 = 0, A1 = 1, B0 = 2, B1 = 3 };
+  __shared__ __attribute__((aligned(1024))) char smem[2 * SLAB];
+
+  int mb, ks, nb;
+  locate_tile(remap_xcd(blockIdx.x, gridDim.x), n_mtiles, n_ntiles, ksplit,
+              ep.m_band, mb, ks, nb);
+  int m_live = M;
+  if constexpr (EPI == EPI_HEAD) m_live = ep.list[0];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+  const int l16 = lane & 15, k4 = lane >> 4;
+  const bool dual = (EPI == EPI_SWIGLU) || (EPI == EPI_PARTIAL && ep.dual);
+  const bool tiled = EPI == EPI_HEAD && ep.b_tiled;
+  const int nk_all = K / 64;
+  const int chunk = (nk_all + ksplit - 1) / ksplit;
+  const int kt0 = ks * chunk;
+  const int nk = min(nk_all, kt0 + chunk) - kt0;
+
+  // row tiles mb, mb + n_mtiles, ... (one, unless the head's grid is narrower
+  // than its live rows)
+  for (int mt = mb; mt * 256 < m_live; mt += n_mtiles) {
+  const int m0 = mt * 256;
+  if (mt != mb) __syncthreads();      // LDS of the previous tile retired
+
+  // The two loads of a half bring rows (wave * 2 + q) * 8 + lane / 8 of it,
+  // 16-byte chunk swizzled.  A lane's byte offsets are the same for both
+  // halves of an operand; rows of A past the last live one lie past the
+  // buffer's end and read as zeros.
+  uint32_t off_a[2], off_b[2];
+  const int b_block = min(nb * 2, (N - 1) >> 7);      // tiled head: 128 rows
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int r = (wave * 2 + q) * 8 + (lane >> 3);
+    const uint32_t c = ((lane & 7) ^ ((r >> 1) & 7)) * 16;
+    off_a[q] = (uint32_t)((r >> 6) * 128 + (r & 63)) * (uint32_t)(K * 2) + c;
+    const int col = block_col<EPI>(r >> 5, (r >> 4) & 1, dual) + (r & 15);
+    if (tiled)
+      off_b[q] = (uint32_t)((min(nb * 2 + (col >> 7), (N - 1) >> 7) - b_block) *
+                                128 + (col & 127)) * 128 + c;
+    else
+      off_b[q] = (uint32_t)col * (uint32_t)(K * 2) + c;
+  }
+  const char* base_a = reinterpret_cast<const char*>(A + (size_t)m0 * K + (size_t)kt0 * 64);
+  const uint32_t size_a =
+      (uint32_t)min(256, m_live - m0) * (uint32_t)(K * 2) - (uint32_t)kt0 * 128;
+  const char *base_b, *base_b1;
+  if (tiled) {
+    base_b = reinterpret_cast<const char*>(B + (size_t)b_block * 128 * 64);
+    base_b1 = base_b + 32 * 128;
+  } else {
+    const size_t at = (size_t)nb * (dual ? 128 : 256) * K + (size_t)kt0 * 64;
+    base_b = reinterpret_cast<const char*>(B + at);
+    base_b1 = dual ? reinterpret_cast<const char*>(B2 + at)
+                   : base_b + (size_t)(EPI == EPI_STORE ? 64 : 32) * K * 2;
+  }
+  // bytes to the next 64 K columns: a tiled head (never split) steps over all
+  // its blocks
+  const size_t b_step = tiled ? (size_t)((N + 127) / 128) * 128 * 64 * 2 : 128;
+  auto issue = [&](int half, int kt) {
+    char* dst = smem + (kt & 1) * SLAB + half * HALF + wave * 2048;
+    if (half < 2) {
+      const uint32_t skip = (uint32_t)kt * 128 + (half ? (uint32_t)K * 128 : 0u);
+      const uint32_t left =
+          __builtin_amdgcn_readfirstlane(skip < size_a ? size_a - skip : 0u);
+      dma16_from(base_a + skip, left, off_a[0], dst);
+      dma16_from(base_a + skip, left, off_a[1], dst + 1024);
+    } else {
+      const char* from = (half == B0 ? base_b : base_b1) + (size_t)kt * b_step;
+      dma16_from(from, 0xffffffffu, off_b[0], dst);
+      dma16_from(from, 0xffffffffu, off_b[1], dst + 1024);
+    }
+  };
+
+  // fragment addresses inside a slab: row wm*64 + i*16 + l16 of a half of A,
+  // wn*32 + j*16 + l16 of B; the swizzle depends on l16 alone
+  const int sw = (l16 >> 1) & 7;
+  const int c0 = (k4 ^ sw) << 4, c1 = ((4 + k4) ^ sw) << 4;
+  const int ra = (wm * 64 + l16) * 128, rb = B0 * HALF + (wn * 32 + l16) * 128;
+  v8 fa[4][2], fb[4][2];
+  // acc[i][j][u]: row wm*128 + i*16 + l16, column block_col(wn, j) + k4*4 + u
+  f32x4 acc[8][4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc[i][j][u] = 0.f;
+  // wave rows past the last live one are not multiplied
+  const bool live0 = m0 + wm * 128 < m_live, live1 = m0 + wm * 128 + 64 < m_live;
+
+  auto section_end = [&] {
+    __builtin_amdgcn_sched_barrier(0);
+    barrier_nofence();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto read_a = [&](const char* s) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      fa[i][0] = *reinterpret_cast<const v8*>(s + ra + i * 2048 + c0);
+      fa[i][1] = *reinterpret_cast<const v8*>(s + ra + i * 2048 + c1);
+    }
+  };
+  auto read_b = [&](const char* s) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const char* r = s + (j >> 1) * HALF + rb + (j & 1) * 2048;
+      fb[j][0] = *reinterpret_cast<const v8*>(r + c0);
+      fb[j][1] = *reinterpret_cast<const v8*>(r + c1);
+    }
+  };
+  // ends a read section: its fragments are in registers, and of the loads all
+  // but the N youngest have landed
+  auto read_end = [&](auto n) {
+    constexpr int N_ = decltype(n)::value;
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N_) : "memory");
+    section_end();
+  };
+  auto multiply = [&](auto qa, bool live) {
+    constexpr int QA = decltype(qa)::value;
+    if (live) {
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[QA * 4 + i][j] =
+                Fmt::mfma16(fb[j][kk], fa[i][kk], acc[QA * 4 + i][j]);
+      __builtin_amdgcn_s_setprio(0);
+    }
+    section_end();
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I8 = std::integral_constant<int, 8>;
+  // LAST = 0: slab kt+2 exists; 1: kt is the last but one; 2: the last
+  auto slab = [&](int kt, auto last) {
+    constexpr int LAST = decltype(last)::value;
+    const char* s = smem + (kt & 1) * SLAB;
+    read_b(s);
+    read_a(s);
+    if constexpr (LAST < 2) {
+      issue(A1, kt + 1);
+      read_end(I8{});
+    } else {
+      read_end(I0{});
+    }
+    multiply(I0{}, live0);
+
+    read_a(s + HALF);
+    if constexpr (LAST == 0) {
+      issue(A0, kt + 2);
+      issue(B0, kt + 2);
+      issue(B1, kt + 2);
+      read_end(I8{});
+    } else {
+      read_end(I2{});
+    }
+    multiply(I1{}, live1);
+  };
+
+  issue(A0, 0);
+  issue(B0, 0);
+  issue(B1, 0);
+  issue(A1, 0);
+  if (nk > 1) {
+    issue(A0, 1);
+    issue(B0, 1);
+    issue(B1, 1);
+    wait_vmcnt<8>();
+  } else {
+    wait_vmcnt<2>();
+  }
+  section_end();
+  if (wm == 1) section_end();
+  for (int kt = 0; kt + 2 < nk; ++kt) slab(kt, I0{});
+  if (nk > 1) slab(nk - 2, I1{});
+  slab(nk - 1, I2{});
+  if (wm == 0) section_end();
+
+  // ---------------------------------------------------------------- epilogue
+  int nf = 0;     // non-finite 16-bit values stored by this lane
+  auto store4 = [&](uint16_t* C, const float (&v)[4]) {
+    uint16_t h[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      h[u] = Fmt::store(v[u]);
+      nf += Fmt::nonfinite(h[u]);
+    }
+    u32x2 w;
+    w[0] = h[0] | (uint32_t)h[1] << 16;
+    w[1] = h[2] | (uint32_t)h[3] << 16;
+    *reinterpret_cast<u32x2*>(C) = w;
+  };
+  const int row0 = m0 + wm * 128 + l16;
+  if constexpr (EPI == EPI_STORE) {
+    uint16_t* C = reinterpret_cast<uint16_t*>(ep.C) + nb * 256;
+    const bool rope = ep.pos && nb * 256 + (wn >> 1) * 128 < ep.rope_cols;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int row = row0 + i * 16;
+      if (row >= M) continue;
+      uint16_t* crow = C + (size_t)row * ep.ldc + k4 * 4;
+      const float2* cs = rope ? ep.cs + (size_t)ep.pos[row] * 64 : nullptr;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int col = block_col<EPI>(wn, j, false);
+        float x[4], y[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { x[u] = acc[i][j][u]; y[u] = acc[i][j + 2][u]; }
+        if (rope) {
+          const float4* c4 = reinterpret_cast<const float4*>(cs + (col & 63) + k4 * 4);
+          const float4 p = c4[0], q = c4[1];
+          const float cc[4] = {p.x, p.z, q.x, q.z}, ss[4] = {p.y, p.w, q.y, q.w};
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float a = x[u], b = y[u];
+            x[u] = a * cc[u] - b * ss[u];
+            y[u] = b * cc[u] + a * ss[u];
+          }
+        }
+        store4(crow + col, x);
+        store4(crow + col + 64, y);
+      }
+    }
+  } else if constexpr (EPI == EPI_ADD_F32) {
+    float* C = reinterpret_cast<float*>(ep.C) + nb * 256 + wn * 64 + k4 * 4;
+    // the residual rows are fetched two blocks of 16 at a time, ahead of the
+    // stores (which the compiler cannot move loads across)
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+      f32x4 x[2][4];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int row = min(row0 + (i + h) * 16, M - 1);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          x[h][j] = *reinterpret_cast<const f32x4*>(C + (size_t)row * ep.ldc + j * 16);
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int row = row0 + (i + h) * 16;
+        if (row >= M) continue;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          f32x4 v;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) v[u] = x[h][j][u] + acc[i + h][j][u];
+          *reinterpret_cast<f32x4*>(C + (size_t)row * ep.ldc + j * 16) = v;
+        }
+      }
+    }
+  } else if constexpr (EPI == EPI_SWIGLU) {
+    uint16_t* C = reinterpret_cast<uint16_t*>(ep.C) + nb * 128;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int row = row0 + i * 16;
+      if (row >= M) continue;
+      uint16_t* crow = C + (size_t)row * ep.ldc + k4 * 4;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        float h[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float g = acc[i][j][u];
+          h[u] = g / (1.0f + __expf(-g)) * acc[i][j + 2][u];
+        }
+        store4(crow + block_col<EPI>(wn, j, true), h);
+      }
+    }
+  } else if constexpr (EPI == EPI_PARTIAL) {
+    float* P = ep.part + (size_t)ks * M * ep.part_ld + k4 * 4;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int row = row0 + i * 16;
+      if (row >= M) continue;
+      float* prow = P + (size_t)row * ep.part_ld;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int c = block_col<EPI>(wn, j, dual);
+        const int col = dual ? (j < 2 ? 0 : ep.ffn) + nb * 128 + (c & 127)
+                             : nb * 256 + c;
+        *reinterpret_cast<f32x4*>(prow + col) = acc[i][j];
+      }
+    }
+  } else {   // EPI_HEAD
+    // (max, sum exp, first argmax) of each row over the tile's 256 columns:
+    // 16 in a lane, then the four lanes of the row, then the four wave columns
+    // through the slabs' LDS, which every wave is done with after the barrier
+    __syncthreads();
+    float* red_m = reinterpret_cast<float*>(smem);      // [4][256] each
+    float* red_s = red_m + 1024;
+    int* red_a = reinterpret_cast<int*>(red_s + 1024);
+    const int col0 = nb * 256 + wn * 64 + k4 * 4;
+    const bool vec = (ep.vocab & 3) == 0 && ((uintptr_t)ep.logits_out & 15) == 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int row = row0 + i * 16;
+      if (ep.logits_out && row < m_live) {
+        float* lrow = ep.logits_out + (size_t)ep.list[1 + row] * ep.vocab;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int col = col0 + j * 16;
+          if (vec) {
+            if (col < ep.vocab) *reinterpret_cast<f32x4*>(lrow + col) = acc[i][j];
+          } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (col + u < ep.vocab) lrow[col + u] = acc[i][j][u];
+          }
+        }
+      }
+      float m = -INFINITY, s = 0.f;
+      int a = 0x7fffffff;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {           // columns ascend: keeps the first
+          const int col = col0 + j * 16 + u;
+          float v = acc[i][j][u];
+          if (col == ep.mask_id || col >= ep.vocab) v = -INFINITY;
+          acc[i][j][u] = v;
+          if (v > m) { m = v; a = col; }
+        }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (acc[i][j][u] != -INFINITY) s += __expf(acc[i][j][u] - m);
+      head_join_lanes<16>(m, s, a);
+      head_join_lanes<32>(m, s, a);
+      if (k4 == 0) {
+        const int o = wn * 256 + wm * 128 + i * 16 + l16;
+        red_m[o] = m;
+        red_s[o] = s;
+        red_a[o] = a;
+      }
+    }
+    __syncthreads();
+    if (t < 256 && m0 + t < m_live) {
+      float m = red_m[t], s = red_s[t];
+      int a = red_a[t];
+#pragma unroll
+      for (int w = 1; w < 4; ++w)
+        head_join(m, s, a, red_m[w * 256 + t], red_s[w * 256 + t], red_a[w * 256 + t]);
+      const size_t o = (size_t)(m0 + t) * ep.n_slabs + nb;
+      ep.pmax[o] = m;
+      ep.psum[o] = s;
+      ep.parg[o] = a;
+    }
+  }
+  if (nf && ep.overflow) atomicAdd(ep.overflow, nf);
+  }  // row tiles
+}
+
+template <typename Fmt, int EPI>
+int launch_phased(const uint16_t* A, const uint16_t* B, const uint16_t* B2,
+                  int M, int N, int K, int ksplit, EpiArgs ep, hipStream_t s,
+                  int max_mtiles = 1 << 30) {
+  const int mt = std::min((M + 255) / 256, max_mtiles);
+  const int nt = (N + 255) / 256;
+  ep.m_band = m_band(mt);
+  hipLaunchKernelGGL((gemm16_phased_kernel<Fmt, EPI>), dim3(mt * nt * ksplit),
+                     dim3(512), 0, s, A, B, B2, M, N, K, mt, nt, ksplit, ep);
   DAVET_HIP(hipGetLastError());
   return DAVET_OK;
 }
@@ -549,17 +1005,21 @@ using V15 = Var<128, 256, 32, 3, 8>;   // 72 KB: tiled vocabulary head
 // the scheduler's interleaving strategy 0; same accumulation order per
 // output, so bit-identical to V13
 using V16 = Var<256, 256, 64, 2, 16, 0, 4>;
+constexpr int PHASED = 17;             // gemm16_phased_kernel
+// its lanes' offsets into 256 rows of K 16-bit values fit 32 bits
+constexpr int PHASED_MAX_K = 1 << 22;
+constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 int variant_bn(int tile) {
   switch (tile) {
-    case 8: case 13: case 15: case 16: return 256;
+    case 8: case 13: case 15: case 16: case 17: return 256;
     default: return 128;
   }
 }
 int variant_bm(int tile) {
   switch (tile) {
     case 14: return 192;
-    case 8: case 13: case 16: return 256;
+    case 8: case 13: case 16: case 17: return 256;
     default: return 128;
   }
 }
@@ -568,7 +1028,7 @@ int variant_bk(int tile) {
 }
 bool variant_known(int tile) {
   return tile == 0 || tile == 6 || tile == 8 || (tile >= 12 && tile <= 14) ||
-         tile == 16;
+         tile == 16 || tile == 17;
 }
 
 template <typename Fmt, int EPI>
@@ -583,6 +1043,8 @@ int launch_shape(const GemmPlan& p, const uint16_t* A, const uint16_t* B,
     case 13: LV(V13);
     case 14: LV(V14);
     case 16: LV(V16);
+    case PHASED:
+      return launch_phased<Fmt, EPI>(A, B, B2, M, N, K, p.ksplit, ep, s);
     default: LV(V0);
   }
 #undef LV
@@ -637,13 +1099,13 @@ constexpr int kNP = 26;
 struct TableShape { int N, K; GemmPlan plan[kNP]; };
 constexpr TableShape kTable[] = {
     // QKV: N = 3d, K = d
-    {12288, 4096, {{8, 5}, {16, 2}, {13, 2}, {16, 2}, {16, 2}, {12, 1}, {16, 3}, {14, 1}, {16, 1}, {16, 1}, {16, 1}, {14, 2}, {14, 2}, {12, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}}},
+    {12288, 4096, {{8, 5}, {14, 2}, {16, 2}, {16, 2}, {16, 2}, {12, 1}, {17, 1}, {17, 1}, {16, 1}, {16, 1}, {16, 1}, {14, 2}, {14, 2}, {17, 1}, {17, 1}, {17, 1}, {16, 1}, {16, 1}, {16, 1}, {17, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {17, 1}, {17, 1}}},
     // output projection: N = d, K = d
-    {4096, 4096, {{6, 8}, {6, 5}, {6, 4}, {6, 4}, {12, 4}, {6, 3}, {6, 2}, {12, 2}, {16, 4}, {6, 2}, {16, 3}, {14, 2}, {14, 2}, {16, 2}, {6, 1}, {14, 1}, {14, 1}, {14, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}}},
+    {4096, 4096, {{6, 8}, {6, 5}, {6, 4}, {6, 4}, {12, 4}, {6, 3}, {6, 2}, {12, 2}, {6, 2}, {6, 2}, {16, 3}, {14, 2}, {14, 2}, {16, 2}, {6, 1}, {14, 1}, {14, 1}, {14, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {14, 1}, {16, 1}, {16, 1}, {17, 1}}},
     // gate + up: N = 2 ffn, K = d
-    {24576, 4096, {{12, 1}, {14, 1}, {14, 1}, {16, 1}, {16, 1}, {12, 1}, {14, 1}, {14, 1}, {14, 1}, {14, 1}, {16, 1}, {14, 1}, {14, 1}, {16, 1}, {16, 1}, {14, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}}},
+    {24576, 4096, {{12, 1}, {14, 1}, {17, 1}, {17, 1}, {17, 1}, {12, 1}, {14, 1}, {14, 1}, {14, 1}, {14, 1}, {16, 1}, {14, 1}, {14, 1}, {17, 1}, {17, 1}, {17, 1}, {16, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}}},
     // down projection: N = d, K = ffn
-    {4096, 12288, {{12, 8}, {14, 8}, {16, 8}, {16, 8}, {8, 8}, {16, 5}, {16, 5}, {8, 5}, {16, 4}, {16, 4}, {16, 3}, {14, 2}, {14, 2}, {16, 2}, {16, 2}, {8, 3}, {14, 1}, {14, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 1}, {16, 2}, {16, 1}, {16, 1}, {16, 1}}},
+    {4096, 12288, {{12, 8}, {14, 8}, {16, 8}, {16, 8}, {8, 8}, {16, 5}, {16, 5}, {8, 5}, {16, 4}, {16, 4}, {16, 3}, {17, 2}, {14, 2}, {16, 2}, {16, 2}, {17, 1}, {17, 1}, {14, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 2}, {17, 1}, {17, 1}, {17, 1}}},
 };
 
 // Row counts just past a multiple of a point's tile height, where the point's
@@ -691,7 +1153,7 @@ static const TableShape* table_shape(int N, int K) {
 static GemmPlan plan_generic(int M, int N, int K) {
   GemmPlan p{};
   const bool big = M >= (N >= 16384 ? 2048 : 3000);
-  p.tile = (big && N % 256 == 0 && K % 64 == 0) ? 16 : (K % 64 == 0 ? 6 : 0);
+  p.tile = (big && N % 256 == 0 && K % 64 == 0 && K <= PHASED_MAX_K) ? PHASED : (K % 64 == 0 ? 6 : 0);
   const int bm = variant_bm(p.tile), bn = variant_bn(p.tile);
   const int tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
   const int nk = K / variant_bk(p.tile);
@@ -749,6 +1211,9 @@ int launch_gemm16(int dtype, int epi, const GemmPlan& plan, const uint16_t* A,
   if (N % variant_bn(plan.tile) || K % variant_bk(plan.tile) ||
       (plan.ksplit > 1 && (K / variant_bk(plan.tile)) < plan.ksplit))
     return set_error(DAVET_ESHAPE, "gemm16: N or K not a multiple of the tile");
+  if (plan.tile == PHASED &&
+      (K > PHASED_MAX_K || ceil_div(K / 64, ceil_div(K / 64, plan.ksplit)) != plan.ksplit))
+    return set_error(DAVET_ESHAPE, "gemm16: K out of range or a K split without work");
   if (plan.ksplit > 1 && !partials)
     return set_error(DAVET_EINVAL, "gemm16: split-K needs a partial buffer");
   ProfScope ps(cls, s);
@@ -783,7 +1248,7 @@ int launch_gemm16(int dtype, int epi, const GemmPlan& plan, const uint16_t* A,
 static int head16_variant(int tiled, int live) {
   if (!tiled) return 12;
   const int n128 = (std::max(live, 1) + 127) / 128;
-  return (n128 == 1 || (n128 % 2 == 1 && n128 <= 5)) ? 15 : 13;
+  return (n128 == 1 || (n128 % 2 == 1 && n128 <= 5)) ? 15 : PHASED;
 }
 
 int head16_slabs(int vocab, int tiled, int live_bound) {
@@ -829,7 +1294,7 @@ int launch_head16(int dtype, const uint16_t* Hm, const uint16_t* W,
 #define HEAD_VARIANTS(Fmt)       \
   switch (variant) {             \
     case 12: HV(Fmt, V12);       \
-    case 13: HV(Fmt, V13);       \
+    case PHASED: return launch_phased<Fmt, EPI_HEAD>(Hm, W, nullptr, max_rows, vocab, d, 1, ep, s, m_slots); \
     case 15: HV(Fmt, V15);       \
   }
   if (dtype == DAVET_F16) {
