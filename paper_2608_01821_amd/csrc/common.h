@@ -235,8 +235,9 @@ struct GemmPlan {
   int tile;      // kernel variant (tile shape, K slab, stages, waves)
   int ksplit;    // > 1: fp32 partials [ksplit][M][N] + a reduction kernel
 };
-// Tile shape and K split for an M x N x K product (N = 2*ffn for SwiGLU).
-GemmPlan plan_gemm16(int M, int N, int K);
+// Tile shape and K split for an M x N x K product (N = 2*ffn for SwiGLU);
+// rotary: its epilogue applies the rotary embedding.
+GemmPlan plan_gemm16(int M, int N, int K, bool rotary = false);
 // 16-bit GEMM with fused epilogue.  EPI_STORE applies the rotary embedding to
 // columns < rope_cols using pos[row] and the cos/sin table cs when pos is
 // given.  With plan.ksplit > 1 the kernel writes fp32 partials to `partials`

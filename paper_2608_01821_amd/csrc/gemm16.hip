@@ -985,7 +985,6 @@ int launch_phased(const uint16_t* A, const uint16_t* B, const uint16_t* B2,
 
 // The kernel variants the planner can pick (index = GemmPlan::tile; the
 // indices are those of the measurement tables, other tiles measured slower).
-using V0 = Var<128, 128, 32, 4, 4>;    // 64 KB LDS, 2 workgroups per CU
 // V6 with the scheduler's interleaving strategy 1: measured on MI355X
 // (candidates interleaved launch by launch, cold weights) never slower on any
 // table entry that uses it, median 5 % faster; the 256 x 256 and 8-wave
@@ -995,15 +994,12 @@ using V0 = Var<128, 128, 32, 4, 4>;    // 64 KB LDS, 2 workgroups per CU
 using V6 = Var<128, 128, 64, 2, 4, 1>; // 64 KB, 2 workgroups per CU
 using V8 = Var<256, 256, 64, 2, 8>;    // 128 KB, deep slabs, large M
 using V12 = Var<128, 128, 64, 2, 8>;   // 64 KB, 8 wavefronts, 2 WG/CU
-using V13 = Var<256, 256, 64, 2, 16>;  // 128 KB, 16 wavefronts
 // 192-row tiles: fewer padded rows and a fuller last wave of workgroups for
 // sequences of ~700-3000 tokens (3 sub-tiles of 32 rows per wave)
 using V14 = Var<192, 128, 64, 2, 4, -1, 2, 1>; // 80 KB, 2 workgroups per CU
 using V15 = Var<128, 256, 32, 3, 8>;   // 72 KB: tiled vocabulary head
-// V13's tile with the 16 wavefronts in a 4 x 4 grid (64 x 64 per wave
-// instead of 32 x 128: a fifth fewer LDS fragment bytes per matrix op) and
-// the scheduler's interleaving strategy 0; same accumulation order per
-// output, so bit-identical to V13
+// 16 wavefronts in a 4 x 4 grid (64 x 64 per wave) with the scheduler's
+// interleaving strategy 0
 using V16 = Var<256, 256, 64, 2, 16, 0, 4>;
 constexpr int PHASED = 17;             // gemm16_phased_kernel
 // its lanes' offsets into 256 rows of K 16-bit values fit 32 bits
@@ -1012,23 +1008,23 @@ constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 int variant_bn(int tile) {
   switch (tile) {
-    case 8: case 13: case 15: case 16: case 17: return 256;
+    case 8: case 15: case 16: case PHASED: return 256;
     default: return 128;
   }
 }
 int variant_bm(int tile) {
   switch (tile) {
     case 14: return 192;
-    case 8: case 13: case 16: case 17: return 256;
+    case 8: case 16: case PHASED: return 256;
     default: return 128;
   }
 }
 int variant_bk(int tile) {
-  return (tile == 0 || tile == 15) ? 32 : 64;
+  return tile == 15 ? 32 : 64;
 }
 bool variant_known(int tile) {
-  return tile == 0 || tile == 6 || tile == 8 || (tile >= 12 && tile <= 14) ||
-         tile == 16 || tile == 17;
+  return tile == 6 || tile == 8 || tile == 12 || tile == 14 || tile == 16 ||
+         tile == PHASED;
 }
 
 template <typename Fmt, int EPI>
@@ -1040,12 +1036,11 @@ int launch_shape(const GemmPlan& p, const uint16_t* A, const uint16_t* B,
     case 6: LV(V6);
     case 8: LV(V8);
     case 12: LV(V12);
-    case 13: LV(V13);
     case 14: LV(V14);
     case 16: LV(V16);
     case PHASED:
       return launch_phased<Fmt, EPI>(A, B, B2, M, N, K, p.ksplit, ep, s);
-    default: LV(V0);
+    default: return set_error(DAVET_EINVAL, "gemm16: unknown tile variant");
   }
 #undef LV
 }
@@ -1088,6 +1083,10 @@ int gemm_dispatch(const GemmPlan& p, int epi, const uint16_t* A,
 // parts then moved three more (192 x 128 at 356, 4 x 4-wave 256 x 256 at 420
 // and 480: 12 % and 6 % faster), and one at 150-250 rows (8-wave 128 x 128
 // without a K split instead of 256 x 256 with two: 2-14 % faster).
+// The phased tile then took the 36 entries where it measured faster (sweep
+// of variants 6, 8, 12, 14, 16 and the phased tile, splits 1-6 and 8): gate/up
+// from 1700 rows and at 356-480, down from 2300 rows, QKV at 650-750 and
+// 1700-2300; 2-9 % each.
 // Because the number of row tiles and of waves of workgroups changes in
 // steps, the best plan is jagged in M; a product of M rows takes the plan of
 // the nearest sample point in log M, except in the ranges of kEdge.
@@ -1147,42 +1146,77 @@ static const TableShape* table_shape(int N, int K) {
   return nullptr;
 }
 
-// Other shapes: 128 x 128 tiles with 128-byte slabs and two workgroups per CU
-// up to ~2-3K rows, 256 x 256 tiles with 16 wavefronts (4 x 4) above; narrow-N
-// products split K until the grid fills the 256 CUs (tiles * ksplit < 512).
-static GemmPlan plan_generic(int M, int N, int K) {
-  GemmPlan p{};
-  const bool big = M >= (N >= 16384 ? 2048 : 3000);
-  p.tile = (big && N % 256 == 0 && K % 64 == 0 && K <= PHASED_MAX_K) ? PHASED : (K % 64 == 0 ? 6 : 0);
-  const int bm = variant_bm(p.tile), bn = variant_bn(p.tile);
-  const int tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-  const int nk = K / variant_bk(p.tile);
-  p.ksplit = 1;
-  if (N < 8192)
-    while (tiles * p.ksplit < 256 && nk / (p.ksplit * 2) >= 16 && p.ksplit < 8)
-      p.ksplit *= 2;
-  return p;
+// Other shapes: the (tile, K split) with the least modelled time, in us.
+// A product costs a start, a K slab of 64 per slab and round of workgroups
+// (less while a tile has its CU to itself), an epilogue per round (the rotary
+// store's scattered 2-byte stores cost the older tiles more, four waves most),
+// for a split the partials through memory and a second kernel, and never less
+// than its weights' stream.  The constants are a fit to 244 products (M 100 -
+// 18020, N 512 - 24576, K 512 - 12288, weights cold, 5-20 plans each, rms
+// error 11 %).  Over 140 of them at five other widths the plan so chosen is
+// on average 3.8 % (at worst 33 %) slower than the best one measured; the rule
+// before it (128 x 128 tiles, K split by powers of two up to 256 tiles for N
+// < 8192, 256 x 256 tiles past 2-3 thousand rows) was 26 % slower.
+struct TileCost { int tile; double single, pair, rotary; };
+constexpr TileCost kTileCost[] = {
+    // us a slab alone on a CU and in a pair (0: never two on a CU), us of
+    // rotary store per round and 256 x 256 elements
+    {6, 0.77, 1.00, 31.0}, {12, 0.71, 1.04, 5.2}, {14, 0.90, 1.36, 31.0},
+    {16, 1.47, 0, 5.2},    {PHASED, 1.50, 0, 0},
+};
+constexpr size_t GENERIC_PARTIALS = (size_t)512 * 256 * 256 * 4;
+
+static GemmPlan plan_generic(int M, int N, int K, bool rotary) {
+  GemmPlan best{12, 1};
+  double best_us = 1e30;
+  const double stream = 2.0 * N * K / 5e6;
+  const int slabs = K / 64;
+  for (const TileCost& c : kTileCost) {
+    const int bm = variant_bm(c.tile), bn = variant_bn(c.tile);
+    if (N % bn || (c.tile == PHASED && K > PHASED_MAX_K)) continue;
+    const double tiles = (double)ceil_div(M, bm) * (N / bn);
+    for (int ks = 1; ks <= 8; ++ks) {
+      const int part = ceil_div(slabs, ks);
+      const double partials = 4.0 * ks * M * N;
+      if (ks == 7) continue;        // the reductions take 2-6 and 8
+      if (ks > 1 && (part < 4 || ceil_div(slabs, part) != ks ||
+                     partials > (double)GENERIC_PARTIALS))
+        continue;
+      const double per_cu = std::ceil(tiles * ks / 256);
+      const double pairs = c.pair > 0 ? std::floor(per_cu / 2) : 0;
+      const double rounds = c.pair > 0 ? std::ceil(per_cu / 2) : per_cu;
+      const double mul = part * (pairs * c.pair + (per_cu - 2 * pairs) * c.single);
+      const double epi = rounds * bm * bn / 65536 *
+                         (3.9 + (rotary && ks == 1 ? c.rotary : 0));
+      const double us = 4.6 + epi + std::max(mul, stream) +
+                        (ks > 1 ? 1.5 + 0.71 * 2 * partials / 5e6 : 0);
+      if (us < best_us) {
+        best_us = us;
+        best = {c.tile, ks};
+      }
+    }
+  }
+  return best;
 }
 
-GemmPlan plan_gemm16(int M, int N, int K) {
+GemmPlan plan_gemm16(int M, int N, int K, bool rotary) {
   if (const TableShape* t = table_shape(N, K)) {
     for (const EdgeRange& e : kEdge)
       if (e.N == N && e.K == K && M >= e.lo && M <= e.hi) return e.plan;
     return t->plan[point_index(M)];
   }
-  return plan_generic(M, N, K);
+  return plan_generic(M, N, K, rotary);
 }
 
 // Largest split-K partial buffer (bytes) any M <= max_M needs.  Table shapes:
 // within a run of rows that share one plan the size grows with M, so the
 // bound is reached at the top of a point's range, of an edge range or of the
-// rows below an edge range (or at max_M).  Other shapes: tiles * ksplit
-// < 512 caps it at 512 tiles of at most 256 x 256.
+// rows below an edge range (or at max_M).  Other shapes: the planner's limit.
 size_t gemm16_partial_bound(int max_M, int N, int K) {
   size_t best = 0;
   auto at = [&](int m) {
     if (m < 1) return;
-    const GemmPlan p = plan_gemm16(m, N, K);
+    const GemmPlan p = plan_gemm16(m, N, K, false);
     if (p.ksplit > 1) best = std::max(best, (size_t)p.ksplit * m * N * 4);
   };
   if (table_shape(N, K)) {
@@ -1195,7 +1229,7 @@ size_t gemm16_partial_bound(int max_M, int N, int K) {
     at(max_M);
     return best;
   }
-  return (size_t)512 * 256 * 256 * 4;
+  return GENERIC_PARTIALS;
 }
 
 int launch_gemm16(int dtype, int epi, const GemmPlan& plan, const uint16_t* A,
@@ -1240,10 +1274,9 @@ int launch_gemm16(int dtype, int epi, const GemmPlan& plan, const uint16_t* A,
 // with 128-column slabs, one round of 494 workgroups; measured on MI355X at
 // V = 126464, d = 4096: 188 -> 181 us at 2 live rows, 262 -> 232 at 128
 // against 128 x 128 tiles); otherwise the head is bound by its matrix work
-// and takes the 256 x 256 projection tile (V13; 192 rows 369 -> 295 us, 1024
-// rows 1361 -> 1198, 2048 rows 2835 -> 2433), whose cost steps with every
-// 256 rows where V15's steps with every 128.  Both read the same columns per
-// lane, so logits and slab partials are the same bits whichever runs.  The
+// and takes the phased 256 x 256 tile, whose cost steps with every 256 rows
+// where V15's steps with every 128.  Logits are the same bits whichever runs;
+// the slab partials' sums are grouped differently.  The
 // row-major layout takes 128 x 128 tiles with 8 wavefronts.
 static int head16_variant(int tiled, int live) {
   if (!tiled) return 12;

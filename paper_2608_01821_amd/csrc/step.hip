@@ -320,7 +320,7 @@ int davet::denoise_step_impl(const davet_model_cfg* cfg, const davet_weights* w,
                            resp_masked, c.mask_id, c.vocab, d, g0, c.rms_eps, X,
                            bf ? A : nullptr, pos, rl, s));
   const int T = sp.total;
-  const GemmPlan p_qkv = plan_gemm16(T, 3 * d, d), p_o = plan_gemm16(T, d, d);
+  const GemmPlan p_qkv = plan_gemm16(T, 3 * d, d, true), p_o = plan_gemm16(T, d, d);
   const GemmPlan p_gu = plan_gemm16(T, 2 * F, d), p_dn = plan_gemm16(T, d, F);
   bool a_ready = true;       // A holds RMSNorm(X) for the next GEMM
   bool hm_ready = false;     // Hm holds the final norm of the masked rows
