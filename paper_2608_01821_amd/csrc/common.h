@@ -205,18 +205,25 @@ struct RowList {
   int32_t* overflow;      // the step's 16-bit overflow counter (may be null)
   int clear_overflow;     // the list builder zeroes it first
 };
-// assembly (and, with A given, the first norm) of every packed row; one extra
-// workgroup builds the masked-row list alongside
+// Rotary table cs[pos][i] = (cos, sin) of pos * theta^(-2 i / head_dim) for
+// pos < max_pos, i < head_dim / 2; max_pos = 0: nothing to build.
+struct RopeTable {
+  int max_pos, head_dim;
+  double theta;
+  float* cs;
+};
+// assembly (and, with A given, the first norm) of every packed row; extra
+// workgroups build the masked-row list and the rotary table alongside
 int launch_assemble_norm(const SeqPack& sp, const ViewPtrs& vp, int dtype,
                          const void* embed, const int32_t* prompt_ids,
                          const int32_t* resp_ids, const uint8_t* masked,
                          int mask_id, int vocab, int d, const float* gain,
                          float eps, float* X, void* A, int32_t* pos,
-                         const RowList& rl, hipStream_t s);
+                         const RowList& rl, const RopeTable& rt,
+                         hipStream_t s);
 int launch_rmsnorm(const float* X, int rows, int d, const float* gain,
                    float eps, int dtype, void* A, hipStream_t s);
-int launch_rope_table(int max_pos, int head_dim, float theta, float* cs,
-                      hipStream_t s);
+int launch_rope_table(const RopeTable& rt, hipStream_t s);
 int launch_final_norm_gather(const float* X, const SeqPack& sp,
                              const int32_t* list, int max_rows, int d,
                              const float* gain, float eps, int dtype, void* Hm,

@@ -169,6 +169,16 @@ __device__ __forceinline__ void build_row_list(const RowList& rl,
   }
 }
 
+// cos/sin of pos * theta^(-2i/D), evaluated in float64 and rounded once.
+__device__ __forceinline__ void rope_entry(const RopeTable& rt, int idx) {
+  const int half = rt.head_dim / 2;
+  if (idx >= rt.max_pos * half) return;
+  const int pos = idx / half, i = idx % half;
+  const double inv = pow(rt.theta, -(2.0 * i) / (double)rt.head_dim);
+  const double a = (double)pos * inv;
+  reinterpret_cast<float2*>(rt.cs)[idx] = make_float2((float)cos(a), (float)sin(a));
+}
+
 // X[row] = [view | E[prompt] | E[resp or mask]] row; A[row] = RMSNorm(X[row])
 // where A is given (the fp32 products norm their rows themselves).
 // One extra workgroup after the rows builds the masked-row list meanwhile.
@@ -180,13 +190,21 @@ assemble_norm_kernel(SeqPack sp, ViewPtrs vp, const T* __restrict__ embed,
                      const uint8_t* __restrict__ masked, int mask_id,
                      int vocab, int d, const float* __restrict__ gain,
                      float eps, float* __restrict__ X, T* __restrict__ A,
-                     int32_t* __restrict__ pos, RowList rl) {
+                     int32_t* __restrict__ pos, RowList rl, RopeTable rt) {
   __shared__ float red[kThreads / 64];
-  const int row = blockIdx.x;
-  if (row == sp.total) {
+  // the row list, the step's rotary table (its launch of its own took 5 us
+  // ahead of these rows), then a row a workgroup
+  int row = blockIdx.x;
+  if (row == 0) {
     build_row_list(rl, masked);
     return;
   }
+  const int rope_blocks = (rt.max_pos * (rt.head_dim / 2) + kThreads - 1) / kThreads;
+  if (row <= rope_blocks) {
+    rope_entry(rt, (row - 1) * kThreads + threadIdx.x);
+    return;
+  }
+  row -= rope_blocks + 1;
   const int s = find_seq(sp, row);
   const int j = row - sp.row0[s];
   if (threadIdx.x == 0 && pos) pos[row] = j;     // rotary position
@@ -242,16 +260,8 @@ rmsnorm_kernel(const float* __restrict__ X, int d,
   norm_store<Fmt>(v, ss, d, gain, eps, A + (size_t)row * d, red);
 }
 
-// cos/sin of pos * theta^(-2i/D), evaluated in float64 and rounded once.
-__global__ void rope_table_kernel(int max_pos, int head_dim, double theta,
-                                  float2* __restrict__ cs) {
-  const int half = head_dim / 2;
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= max_pos * half) return;
-  const int pos = idx / half, i = idx % half;
-  const double inv = pow(theta, -(2.0 * i) / (double)head_dim);
-  const double a = (double)pos * inv;
-  cs[idx] = make_float2((float)cos(a), (float)sin(a));
+__global__ void rope_table_kernel(RopeTable rt) {
+  rope_entry(rt, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // Hm[j] = RMSNorm_final(X[packed row of masked position list[1+j]]).
@@ -659,13 +669,15 @@ int launch_assemble_norm(const SeqPack& sp, const ViewPtrs& vp, int dtype,
                          const int32_t* resp_ids, const uint8_t* masked,
                          int mask_id, int vocab, int d, const float* gain,
                          float eps, float* X, void* A, int32_t* pos,
-                         const RowList& rl, hipStream_t s) {
+                         const RowList& rl, const RopeTable& rt,
+                         hipStream_t s) {
   ProfScope ps(KC_ASSEMBLE, s);
+  const int rope_blocks = (rt.max_pos * (rt.head_dim / 2) + kThreads - 1) / kThreads;
 #define ASM(F)                                                               \
-  hipLaunchKernelGGL(assemble_norm_kernel<F>, dim3(sp.total + 1),             \
+  hipLaunchKernelGGL(assemble_norm_kernel<F>, dim3(sp.total + 1 + rope_blocks), \
                      dim3(kThreads), 0, s, sp, vp, (const F::st*)embed,       \
                      prompt_ids, resp_ids, masked, mask_id, vocab, d, gain,   \
-                     eps, X, (F::st*)A, pos, rl)
+                     eps, X, (F::st*)A, pos, rl, rt)
   if (dtype == DAVET_BF16) ASM(BF16S);
   else if (dtype == DAVET_F16) ASM(F16S);
   else ASM(F32S);
@@ -687,12 +699,10 @@ int launch_rmsnorm(const float* X, int rows, int d, const float* gain,
   return DAVET_OK;
 }
 
-int launch_rope_table(int max_pos, int head_dim, float theta, float* cs,
-                      hipStream_t s) {
+int launch_rope_table(const RopeTable& rt, hipStream_t s) {
   ProfScope ps(KC_MISC, s);
-  const int n = max_pos * (head_dim / 2);
-  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, s,
-                     max_pos, head_dim, (double)theta, (float2*)cs);
+  const int n = rt.max_pos * (rt.head_dim / 2);
+  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, s, rt);
   DAVET_HIP(hipGetLastError());
   return DAVET_OK;
 }

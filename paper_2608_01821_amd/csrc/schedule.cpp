@@ -215,8 +215,8 @@ extern "C" int davet_run_schedule(
   // (a step's sequences are never longer than at the full view)
   float* rope = reinterpret_cast<float*>(ws + rope_off);
   {
-    int rc = launch_rope_table((int)max_len, cfg->head_dim, cfg->rope_theta,
-                               rope, stream);
+    int rc = launch_rope_table(
+        {(int)max_len, cfg->head_dim, (double)cfg->rope_theta, rope}, stream);
     if (rc) return rc;
   }
 

@@ -309,16 +309,15 @@ int davet::denoise_step_impl(const davet_model_cfg* cfg, const davet_weights* w,
   hipStream_t s = stream;
 
 #define RUN(x) do { int rc_ = (x); if (rc_) return rc_; } while (0)
-  if (!rope_cs)
-    RUN(launch_rope_table(max_n, c.head_dim, c.rope_theta,
-                          reinterpret_cast<float*>(ws + lay.rope), s));
+  const RopeTable rt{rope_cs ? 0 : max_n, c.head_dim, (double)c.rope_theta,
+                     reinterpret_cast<float*>(ws + lay.rope)};
   const float* g0 = c.n_layers > 0 ? w->layers[0].attn_norm : w->final_norm;
   int32_t* overflow = reinterpret_cast<int32_t*>(ws + lay.flags);
   const RowList rl{n_seqs * L, list,     conf_out,      argmax_out,
                    slot,       overflow, clear_overflow};
   RUN(launch_assemble_norm(sp, vp, c.dtype, w->embed, prompt_ids, resp_ids,
                            resp_masked, c.mask_id, c.vocab, d, g0, c.rms_eps, X,
-                           bf ? A : nullptr, pos, rl, s));
+                           bf ? A : nullptr, pos, rl, rt, s));
   const int T = sp.total;
   const GemmPlan p_qkv = plan_gemm16(T, 3 * d, d, true), p_o = plan_gemm16(T, d, d);
   const GemmPlan p_gu = plan_gemm16(T, 2 * F, d), p_dn = plan_gemm16(T, d, F);
