@@ -11,8 +11,10 @@
 // chunk c of row r sits in slot c ^ ((r / rows-per-256-bytes) % chunks),
 // which spreads the 16-byte fragment reads of 16 consecutive rows over
 // distinct bank groups.  Workgroup ids are remapped so each XCD (ids
-// congruent mod 8) walks a contiguous run of tiles, M fastest: a weight tile
-// is fetched into one XCD's L2 and reused by every M tile.  The variants
+// congruent mod 8) walks a contiguous run of tiles, in bands of row tiles, M
+// fastest: a weight tile is fetched into one XCD's L2 and reused by the band.
+// Long products and the large vocabulary head run a kernel of their own
+// (gemm16_phased_kernel).  The variants
 // (tile, slab depth, ring depth, waves) and the plan that picks one per
 // product shape are listed after the kernel.
 //
@@ -591,6 +593,14 @@ __device__ __forceinline__ void head_join_lanes(float& m, float& s, int& a) {
 // phases before their first use.  What the next phase reads has landed once at
 // most the eight youngest loads are outstanding.
 //
+// What bounds it: the part's power-limited clock and the hand-over between
+// sections.  Gate/up of d = 4096, ffn = 12288 at 8000 rows, cold weights: the
+// 16-wave tile 1284 us, this one 1260 (1.28 PFLOP/s; matrix pipes busy 68 %
+// against 63 %); down 697 -> 671; at 3092 rows 538 -> 528 and 298 -> 290.
+// Four phases of 16 matrix ops were 3 % slower; fragments read a phase ahead
+// with two barriers a slab were as fast as the 16-wave tile; all loads of one
+// tile's addresses (no cache misses) gain 3 %.
+//
 // The matrix ops take the weights as their first operand, so a lane holds four
 // consecutive columns of one row per accumulator and stores (and, for the
 // residual, loads) them as one vector.  Column block j of wave column wn is
@@ -1075,8 +1085,8 @@ int gemm_dispatch(const GemmPlan& p, int epi, const uint16_t* A,
 // third sweep (variants 4, 6-9 and 12-14, splits 1-6 and 8, the split-K
 // reduction or the following norm included) changed thirteen entries whose
 // new plan was more than 4 % faster in each of three repetitions.  The
-// 4 x 4-wave tile (V16) then replaced V13 wherever it was not slower, timed
-// interleaved on every entry: median 5.8 % faster, bit-identical outputs.
+// 4 x 4-wave tile (V16) then replaced an 8 x 2 one wherever it was not slower,
+// timed interleaved on every entry: median 5.8 % faster, bit-identical outputs.
 // A last interleaved sweep over the current variants (6, 8, 12, 13, 14, 16
 // with their scheduling hints, splits 1-6 and 8) moved 21 entries whose new
 // plan was at least 3 % faster; a check of gate/up at 330-520 rows on two
