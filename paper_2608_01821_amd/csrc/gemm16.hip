@@ -1093,7 +1093,7 @@ int gemm_dispatch(const GemmPlan& p, int epi, const uint16_t* A,
 // parts then moved three more (192 x 128 at 356, 4 x 4-wave 256 x 256 at 420
 // and 480: 12 % and 6 % faster), and one at 150-250 rows (8-wave 128 x 128
 // without a K split instead of 256 x 256 with two: 2-14 % faster).
-// The phased tile then took the 36 entries where it measured faster (sweep
+// The phased tile then took the 35 entries where it measured faster (sweep
 // of variants 6, 8, 12, 14, 16 and the phased tile, splits 1-6 and 8): gate/up
 // from 1700 rows and at 356-480, down from 2300 rows, QKV at 650-750 and
 // 1700-2300; 2-9 % each.
@@ -1162,8 +1162,8 @@ static const TableShape* table_shape(int N, int K) {
 // store's scattered 2-byte stores cost the older tiles more, four waves most),
 // for a split the partials through memory and a second kernel, and never less
 // than its weights' stream.  The constants are a fit to 244 products (M 100 -
-// 18020, N 512 - 24576, K 512 - 12288, weights cold, 5-20 plans each, rms
-// error 11 %).  Over 140 of them at five other widths the plan so chosen is
+// 18020, N 512 - 24576, K 512 - 12288, weights cold, the 5-8 best plans of
+// each, rms error 11 %).  Over 140 of them at five other widths the plan so chosen is
 // on average 3.8 % (at worst 33 %) slower than the best one measured; the rule
 // before it (128 x 128 tiles, K split by powers of two up to 256 tiles for N
 // < 8192, 256 x 256 tiles past 2-3 thousand rows) was 26 % slower.
