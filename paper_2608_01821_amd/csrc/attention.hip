@@ -572,6 +572,15 @@ attn_f32_kernel(const float* __restrict__ qkv, float* __restrict__ out,
 #pragma unroll
       for (int j = 0; j < NB; ++j) vd[j][r] = vp[16 * j];
     }
+    // keys past the last one are zeros: their weight 0 times an infinite value
+    // would be NaN
+    if (kb * 16 + 16 > N) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+          if (kb * 16 + 4 * g + r >= N) vd[j][r] = 0.f;
+    }
   };
   if (wave < nb) load(wave, kf, vf);
   for (int kb = wave; kb < nb; kb += 4) {
@@ -595,11 +604,13 @@ attn_f32_kernel(const float* __restrict__ qkv, float* __restrict__ out,
     mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     const float mn = fmaxf(m, mx);
-    const float al = expf(m - mn);
+    // while every score so far is -inf their weights are 0, not exp(-inf + inf)
+    const float ref = mn == -INFINITY ? 0.f : mn;
+    const float al = expf(m - ref);
     float p[4], ps = 0.f;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      p[r] = expf(sc[r] - mn);
+      p[r] = expf(sc[r] - ref);
       ps += p[r];
     }
     ps += __shfl_xor(ps, 16, 64);
