@@ -540,17 +540,27 @@ struct CsrLevels {
   int n[DAVET_MAX_LEVELS];
 };
 
-// Prune: token t is row mem[t] of v, copied (16 bytes a thread; row_bytes is
-// a multiple of 16).
+// Prune: token t is row mem[t] of v (16 bytes a thread; rows are a multiple of
+// 16 bytes), as the mean of that one row: 0 + x, so that -0 comes out as +0.
+template <typename Fmt>
 __global__ void __launch_bounds__(256)
-copy_rows_kernel(const char* __restrict__ v, CsrLevels lv, int row_bytes) {
+copy_rows_kernel(const typename Fmt::st* __restrict__ v, CsrLevels lv, int d) {
+  constexpr int VEC = 16 / (int)sizeof(typename Fmt::st);
   int l = 0, t = blockIdx.x;
   while (t >= lv.n[l]) t -= lv.n[l++];
-  const int e0 = (blockIdx.y * 256 + threadIdx.x) * 16;
-  if (e0 >= row_bytes) return;
-  *reinterpret_cast<u32x4*>(static_cast<char*>(lv.out[l]) + (size_t)t * row_bytes +
-                            e0) =
-      *reinterpret_cast<const u32x4*>(v + (size_t)lv.mem[l][t] * row_bytes + e0);
+  const int e0 = (blockIdx.y * 256 + threadIdx.x) * VEC;
+  if (e0 >= d) return;
+  u32x4 w = *reinterpret_cast<const u32x4*>(v + (size_t)lv.mem[l][t] * d + e0);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if constexpr (VEC == 8)
+      w[q] = (uint32_t)Fmt::store(0.f + Fmt::load((uint16_t)(w[q] & 0xffffu))) |
+             (uint32_t)Fmt::store(0.f + Fmt::load((uint16_t)(w[q] >> 16))) << 16;
+    else
+      w[q] = __float_as_uint(0.f + __uint_as_float(w[q]));
+  }
+  *reinterpret_cast<u32x4*>(reinterpret_cast<typename Fmt::st*>(lv.out[l]) +
+                            (size_t)t * d + e0) = w;
 }
 
 // Merge: token t = float64 sum of rows mem[offs[t] .. offs[t+1]) of v in that
@@ -738,11 +748,17 @@ int launch_maps(const davet_view_geom& g, const double* keys, const MapPtrs& mp,
 }
 
 template <typename Fmt>
-void launch_pool_csr_t(const void* v, const CsrLevels& lv, int n_tok, int d,
-                       hipStream_t s) {
-  hipLaunchKernelGGL(pool_csr_kernel<Fmt>, dim3(n_tok, (d + 511) / 512),
-                     dim3(256), 0, s,
-                     reinterpret_cast<const typename Fmt::st*>(v), lv, d);
+void launch_level_rows_t(const davet_view_geom& g, const void* v,
+                         const CsrLevels& lv, int n_tok, hipStream_t s) {
+  const auto* vv = reinterpret_cast<const typename Fmt::st*>(v);
+  const int copied = 4096 / (int)sizeof(typename Fmt::st);   // features a block
+  if (g.realizer == DAVET_REALIZER_PRUNE)
+    hipLaunchKernelGGL(copy_rows_kernel<Fmt>,
+                       dim3(n_tok, (g.d + copied - 1) / copied), dim3(256), 0,
+                       s, vv, lv, g.d);
+  else
+    hipLaunchKernelGGL(pool_csr_kernel<Fmt>, dim3(n_tok, (g.d + 511) / 512),
+                       dim3(256), 0, s, vv, lv, g.d);
 }
 
 // Scratch layout: keys, then (offsets, members) of each level < K-1, each
@@ -813,17 +829,9 @@ int build_views_realizer(const davet_view_geom& g, const void* v,
     n_tok += lv.n[l];
   }
   if (n_tok == 0) return DAVET_OK;               // K = 1
-  if (g.realizer == DAVET_REALIZER_PRUNE) {
-    const int row_bytes = g.d * (int)dtype_size(g.dtype);
-    hipLaunchKernelGGL(copy_rows_kernel, dim3(n_tok, (row_bytes + 4095) / 4096),
-                       dim3(256), 0, s, static_cast<const char*>(v), lv, row_bytes);
-  } else if (g.dtype == DAVET_BF16) {
-    launch_pool_csr_t<BF16S>(v, lv, n_tok, g.d, s);
-  } else if (g.dtype == DAVET_F16) {
-    launch_pool_csr_t<F16S>(v, lv, n_tok, g.d, s);
-  } else {
-    launch_pool_csr_t<F32S>(v, lv, n_tok, g.d, s);
-  }
+  if (g.dtype == DAVET_BF16) launch_level_rows_t<BF16S>(g, v, lv, n_tok, s);
+  else if (g.dtype == DAVET_F16) launch_level_rows_t<F16S>(g, v, lv, n_tok, s);
+  else launch_level_rows_t<F32S>(g, v, lv, n_tok, s);
   DAVET_HIP(hipGetLastError());
   return DAVET_OK;
 }

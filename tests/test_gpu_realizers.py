@@ -303,3 +303,32 @@ def test_run_schedule_builds_realizer_views(name):
             got = _levels_to_f32(bufs[i * (cfg.K - 1) + l], mode)
             assert np.array_equal(got, ref[l]), (i, l)
     assert int(msk.sum()) == n * (L - min(L, T * cfg.k))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_prune_rows_bitwise(dtype):
+    """A kept token is the mean of its own row, bit for bit: every value of the
+    format's range as it is (subnormal, largest, infinite), -0 as +0.  d spans
+    two blocks of features and a tail."""
+    C, G, d = 1, 6, 4104
+    rng = np.random.default_rng(5)
+    dev, host = _encoding(rng, C, G, d, dtype)
+    tiny = {"f16": 2.0 ** -24, "bf16": 2.0 ** -133, "f32": 2.0 ** -149}[dtype]
+    top = {"f16": 65504.0, "bf16": 3.3895314e38, "f32": 3.4028235e38}[dtype]
+    special = np.array([-0.0, 0.0, tiny, -tiny, -3 * tiny, top, -top, np.inf,
+                        -np.inf], np.float64).astype(np.float32)
+    at = rng.random(host.shape) < 0.3
+    host[at] = rng.choice(special, int(at.sum()))
+    host[:, -1] = -0.0
+    dev, host = to_mode(host, dtype)
+    geom = dv.ViewGeom(C, G, d, 3, DTYPE[dtype], 0, RZ["prune"])
+    sizes = dv.davet_view_sizes(geom)
+    lv = [torch.empty((n, d), dtype=torch.from_numpy(dev).dtype, device="cuda")
+          for n in sizes[:2]]
+    dv.davet_build_views(geom, torch.from_numpy(dev).cuda(), lv)
+    maps = R.prune_index_maps(R.prune_keys(host, C, G), C, G, 3)
+    for l in range(2):
+        rows = host[maps[l][1]]
+        ref = np.where(rows == 0, np.float32(0), rows)
+        got = _levels_to_f32(lv[l], dtype)
+        assert np.array_equal(got.view(np.uint32), ref.view(np.uint32))
