@@ -332,3 +332,13 @@ def test_prune_rows_bitwise(dtype):
         ref = np.where(rows == 0, np.float32(0), rows)
         got = _levels_to_f32(lv[l], dtype)
         assert np.array_equal(got.view(np.uint32), ref.view(np.uint32))
+
+
+@pytest.mark.parametrize("name", ["prune", "merge"])
+@pytest.mark.parametrize("G", [3, 4, 8, 11, 12, 16, 17, 23, 32, 33, 45, 46])
+def test_maps_at_sort_sizes(name, G):
+    """Key and token counts at and next to the powers of two at which the sort
+    network ends (64, 1024 tokens; 480, 1012, 1984 edges) and on both sides of
+    the 256 keys up to which they are ranked instead (256 and 289 tokens, 220 and
+    264 edges), on keys with ties."""
+    test_maps_from_given_keys_bit_exact(name, 2, G, 3)
