@@ -1,5 +1,5 @@
 // Row-wise kernels of the denoiser step: sequence assembly + embedding gather
-// fused with the first RMSNorm, RMSNorm, rotary embedding, masked-row
+// fused with the first RMSNorm, RMSNorm, the rotary table, masked-row
 // compaction, final norm of the masked rows, and the vocabulary-reduction
 // merge.  One workgroup (4 wavefronts) per row; reductions are wavefront
 // butterflies followed by a 4-entry LDS combine.
@@ -181,7 +181,8 @@ __device__ __forceinline__ void rope_entry(const RopeTable& rt, int idx) {
 
 // X[row] = [view | E[prompt] | E[resp or mask]] row; A[row] = RMSNorm(X[row])
 // where A is given (the fp32 products norm their rows themselves).
-// One extra workgroup after the rows builds the masked-row list meanwhile.
+// The first workgroup builds the masked-row list and the next ones the step's
+// rotary table meanwhile.
 template <typename Fmt, typename T = typename Fmt::st>
 __global__ void __launch_bounds__(kThreads)
 assemble_norm_kernel(SeqPack sp, ViewPtrs vp, const T* __restrict__ embed,
@@ -192,8 +193,7 @@ assemble_norm_kernel(SeqPack sp, ViewPtrs vp, const T* __restrict__ embed,
                      float eps, float* __restrict__ X, T* __restrict__ A,
                      int32_t* __restrict__ pos, RowList rl, RopeTable rt) {
   __shared__ float red[kThreads / 64];
-  // the row list, the step's rotary table (its launch of its own took 5 us
-  // ahead of these rows), then a row a workgroup
+  // (the rotary table's launch of its own took 5 us ahead of these rows)
   int row = blockIdx.x;
   if (row == 0) {
     build_row_list(rl, masked);
@@ -688,6 +688,7 @@ int launch_assemble_norm(const SeqPack& sp, const ViewPtrs& vp, int dtype,
 
 int launch_rmsnorm(const float* X, int rows, int d, const float* gain,
                    float eps, int dtype, void* A, hipStream_t s) {
+  if (!is16(dtype)) return set_error(DAVET_EDTYPE, "rmsnorm: 16-bit outputs only");
   ProfScope ps(KC_RMSNORM, s);
 #define RMS(F)                                                             \
   hipLaunchKernelGGL(rmsnorm_kernel<F>, dim3(rows), dim3(kThreads), 0, s, X, \
@@ -711,6 +712,8 @@ int launch_final_norm_gather(const float* X, const SeqPack& sp,
                              const int32_t* list, int max_rows, int d,
                              const float* gain, float eps, int dtype, void* Hm,
                              hipStream_t s) {
+  if (!is16(dtype))
+    return set_error(DAVET_EDTYPE, "final_norm_gather: 16-bit outputs only");
   ProfScope ps(KC_HEAD_PREP, s);
 #define FNG(F)                                                              \
   hipLaunchKernelGGL(final_norm_gather_kernel<F>, dim3(max_rows),            \
