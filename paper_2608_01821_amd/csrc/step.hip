@@ -2,18 +2,21 @@
 // layout it uses.  The host side only validates, packs the per-sequence table
 // and enqueues kernels; every arithmetic step runs on the GPU.
 //
-// Layer schedule (pre-norm, n_layers times):
+// Layer schedule (pre-norm, n_layers times) of the 16-bit path:
 //   A = RMSNorm(X)                 (fused into the assembly for layer 0, and
-//                                   into the previous layer's tail otherwise)
-//   QKV = A Wqkv^T                 GEMM, bf16 out
-//   rotary embedding on Q, K       in place
+//                                   into the previous layer's tail where that
+//                                   sums K splits)
+//   QKV = A Wqkv^T                 GEMM, 16-bit out, rotary embedding on Q and
+//                                   K in the epilogue (or the split reduction)
 //   O = attention(Q, K, V)         non-causal, per sequence
 //   X += O Wo^T                    GEMM, fp32 residual epilogue
-//   A = RMSNorm(X)
+//   A = RMSNorm(X)                 (in the split reduction where there is one)
 //   H = silu(A Wg^T) * (A Wu^T)    dual GEMM, SwiGLU epilogue
 //   X += H Wd^T                    GEMM, fp32 residual epilogue
 // then the final norm of the masked response rows, the vocabulary GEMM with
 // the fused (max, argmax, sum-exp) reduction, and the merge across slabs.
+// The fp32 path runs the same layer with every norm, the rotary embedding and
+// the gather of the masked rows inside the products: five launches a layer.
 
 #include <algorithm>
 #include <vector>
@@ -319,8 +322,13 @@ int davet::denoise_step_impl(const davet_model_cfg* cfg, const davet_weights* w,
                            resp_masked, c.mask_id, c.vocab, d, g0, c.rms_eps, X,
                            bf ? A : nullptr, pos, rl, rt, s));
   const int T = sp.total;
-  const GemmPlan p_qkv = plan_gemm16(T, 3 * d, d, true), p_o = plan_gemm16(T, d, d);
-  const GemmPlan p_gu = plan_gemm16(T, 2 * F, d), p_dn = plan_gemm16(T, d, F);
+  GemmPlan p_qkv{}, p_o{}, p_gu{}, p_dn{};
+  if (bf) {
+    p_qkv = plan_gemm16(T, 3 * d, d, true);
+    p_o = plan_gemm16(T, d, d);
+    p_gu = plan_gemm16(T, 2 * F, d);
+    p_dn = plan_gemm16(T, d, F);
+  }
   bool a_ready = true;       // A holds RMSNorm(X) for the next GEMM
   bool hm_ready = false;     // Hm holds the final norm of the masked rows
   for (int l = 0; l < c.n_layers; ++l) {
