@@ -99,6 +99,13 @@ struct BF16 {
   __device__ static __forceinline__ uint32_t store2(float a, float b) {
     return (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16);
   }
+  // a * b and a * b + c, rounded
+  __device__ static __forceinline__ uint16_t store_mul(float a, float b) {
+    return f32_to_bf16(a * b);
+  }
+  __device__ static __forceinline__ uint16_t store_fma(float a, float b, float c) {
+    return f32_to_bf16(__builtin_fmaf(a, b, c));
+  }
   __device__ static __forceinline__ uint16_t from_f64(double x) { return f64_to_bf16(x); }
   // 1 when a stored value is not finite (all exponent bits set)
   __device__ static __forceinline__ int nonfinite(uint16_t h) {
@@ -123,6 +130,19 @@ struct F16 {
     typedef _Float16 h2 __attribute__((ext_vector_type(2)));
     const f2 v = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, h2));
+  }
+  // a * b and a * b + c, rounded once: the multiply-add with a 16-bit result
+  // (v_fma_mixlo_f16).  The empty asm keeps the compiler from pairing the
+  // conversions, which would then round an fp32 result again.
+  __device__ static __forceinline__ uint16_t store_mul(float a, float b) {
+    uint32_t h = f32_to_f16(a * b);
+    asm("" : "+v"(h));
+    return (uint16_t)h;
+  }
+  __device__ static __forceinline__ uint16_t store_fma(float a, float b, float c) {
+    uint32_t h = f32_to_f16(__builtin_fmaf(a, b, c));
+    asm("" : "+v"(h));
+    return (uint16_t)h;
   }
   __device__ static __forceinline__ uint16_t from_f64(double x) { return f64_to_f16(x); }
   // 1 when a stored value is not finite: for fp16 a result above 65504 in

@@ -807,13 +807,9 @@ gemm16_phased_kernel(const uint16_t* __restrict__ A,
 
   // ---------------------------------------------------------------- epilogue
   int nf = 0;     // non-finite 16-bit values stored by this lane
-  auto store4 = [&](uint16_t* C, const float (&v)[4]) {
-    uint16_t h[4];
+  auto store4 = [&](uint16_t* C, const uint16_t (&h)[4]) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      h[u] = Fmt::store(v[u]);
-      nf += Fmt::nonfinite(h[u]);
-    }
+    for (int u = 0; u < 4; ++u) nf += Fmt::nonfinite(h[u]);
     u32x2 w;
     w[0] = h[0] | (uint32_t)h[1] << 16;
     w[1] = h[2] | (uint32_t)h[3] << 16;
@@ -832,18 +828,23 @@ gemm16_phased_kernel(const uint16_t* __restrict__ A,
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const int col = block_col<EPI>(wn, j, false);
-        float x[4], y[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) { x[u] = acc[i][j][u]; y[u] = acc[i][j + 2][u]; }
+        uint16_t x[4], y[4];
         if (rope) {
           const float4* c4 = reinterpret_cast<const float4*>(cs + (col & 63) + k4 * 4);
           const float4 p = c4[0], q = c4[1];
           const float cc[4] = {p.x, p.z, q.x, q.z}, ss[4] = {p.y, p.w, q.y, q.w};
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            const float a = x[u], b = y[u];
-            x[u] = a * cc[u] - b * ss[u];
-            y[u] = b * cc[u] + a * ss[u];
+            const float a = acc[i][j][u], b = acc[i][j + 2][u];
+            // contracted as in the other tiles' epilogue: the same bits
+            x[u] = Fmt::store_fma(a, cc[u], -(b * ss[u]));
+            y[u] = Fmt::store_fma(a, ss[u], b * cc[u]);
+          }
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            x[u] = Fmt::store(acc[i][j][u]);
+            y[u] = Fmt::store(acc[i][j + 2][u]);
           }
         }
         store4(crow + col, x);
@@ -886,11 +887,11 @@ gemm16_phased_kernel(const uint16_t* __restrict__ A,
       uint16_t* crow = C + (size_t)row * ep.ldc + k4 * 4;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        float h[4];
+        uint16_t h[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const float g = acc[i][j][u];
-          h[u] = g / (1.0f + __expf(-g)) * acc[i][j + 2][u];
+          h[u] = Fmt::store_mul(g / (1.0f + __expf(-g)), acc[i][j + 2][u]);
         }
         store4(crow + block_col<EPI>(wn, j, true), h);
       }
