@@ -1162,25 +1162,29 @@ static const TableShape* table_shape(int N, int K) {
 // (less while a tile has its CU to itself), an epilogue per round (the rotary
 // store's scattered 2-byte stores cost the older tiles more, four waves most),
 // for a split the partials through memory and a second kernel, and never less
-// than its weights' stream.  The constants are a fit to 244 products (M 100 -
-// 18020, N 512 - 24576, K 512 - 12288, weights cold, the 5-8 best plans of
-// each, rms error 11 %).  Over 140 of them at five other widths the plan so chosen is
-// on average 3.8 % (at worst 33 %) slower than the best one measured; the rule
-// before it (128 x 128 tiles, K split by powers of two up to 256 tiles for N
-// < 8192, 256 x 256 tiles past 2-3 thousand rows) was 26 % slower.
-struct TileCost { int tile; double single, pair, rotary; };
+// than its weights' stream.  The constants are a fit to 644 products at fifteen
+// widths (M 100 - 9000, d 512 - 8192, weights cold; every tile, splits 1 - 6 and
+// 8): the plan so chosen is on average 1.5 % slower than the best one measured,
+// 0.6 % over the summed times.  Constants fitted to one half of the widths do as
+// well on the other (1.6 % and 0.5 %).  With the two 256 x 256 tiles priced
+// alike the older one always won: 3.2 % and 4.2 %, although the phased tile takes
+// 0.92 - 0.99 of its time at K splits of one.  A rule by row counts alone (128 x
+// 128 tiles, K split by powers of two up to 256 tiles for N < 8192, 256 x 256
+// tiles past 2-3 thousand rows) was 26 % slower over 140 products.
+struct TileCost { int tile; double single, pair, epilogue, rotary; };
 constexpr TileCost kTileCost[] = {
     // us a slab alone on a CU and in a pair (0: never two on a CU), us of
-    // rotary store per round and 256 x 256 elements
-    {6, 0.77, 1.00, 31.0}, {12, 0.71, 1.04, 5.2}, {14, 0.90, 1.36, 31.0},
-    {16, 1.47, 0, 5.2},    {PHASED, 1.50, 0, 0},
+    // epilogue, and of rotary store, per round and 256 x 256 elements
+    {6, 0.89, 1.00, 3.9, 31.0}, {12, 0.82, 1.04, 3.6, 4.5},
+    {14, 1.00, 1.36, 4.8, 35.0}, {16, 1.75, 0, 2.0, 5.2},
+    {PHASED, 1.30, 0, 6.5, 0},
 };
 constexpr size_t GENERIC_PARTIALS = (size_t)512 * 256 * 256 * 4;
 
 static GemmPlan plan_generic(int M, int N, int K, bool rotary) {
   GemmPlan best{12, 1};
   double best_us = 1e30;
-  const double stream = 2.0 * N * K / 5e6;
+  const double stream = 2.0 * N * K / 6.6e6;
   const int slabs = K / 64;
   for (const TileCost& c : kTileCost) {
     const int bm = variant_bm(c.tile), bn = variant_bn(c.tile);
@@ -1198,9 +1202,9 @@ static GemmPlan plan_generic(int M, int N, int K, bool rotary) {
       const double rounds = c.pair > 0 ? std::ceil(per_cu / 2) : per_cu;
       const double mul = part * (pairs * c.pair + (per_cu - 2 * pairs) * c.single);
       const double epi = rounds * bm * bn / 65536 *
-                         (3.9 + (rotary && ks == 1 ? c.rotary : 0));
+                         (c.epilogue + (rotary && ks == 1 ? c.rotary : 0));
       const double us = 4.6 + epi + std::max(mul, stream) +
-                        (ks > 1 ? 1.5 + 0.71 * 2 * partials / 5e6 : 0);
+                        (ks > 1 ? 1.0 + 0.9 * 2 * partials / 5e6 : 0);
       if (us < best_us) {
         best_us = us;
         best = {c.tile, ks};

@@ -34,6 +34,9 @@ _launch_gemm16 = _fn(
     _i, _i, _i, C.POINTER(GemmPlan), _p, _p, _p, _p, _i, _i, _i, _i, _p, _p, _i,
     _p, C.c_size_t, _i, _p, _p)
 
+gemm16_partial_bound = _fn("_ZN5davet20gemm16_partial_boundEiii", C.c_size_t,
+                           _i, _i, _i)
+
 EPI_STORE, EPI_ADD_F32, EPI_SWIGLU = 0, 1, 2
 
 

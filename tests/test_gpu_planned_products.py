@@ -1,9 +1,10 @@
-"""The 16-bit products of models other than the 8B-shaped one at the edges of
-what the planner picks, against the oracle: the phased 256 x 256 tile at, one
-past and between multiples of the tile and of the 64 rows a wave skips, with
-one and several bands of row tiles, as the vocabulary head with a ragged last
-slab, odd vocabulary widths and two row tiles; and short sequences whose
-projections (gate and up among them) are split over K.
+"""Steps of 16-bit models other than the 8B-shaped one at the edges of what
+the planner picks, against the oracle: the phased 256 x 256 tile's rotary QKV
+at, one past and between multiples of the tile and of the 64 rows a wave skips,
+with one and several bands of row tiles; its gate/up and split down projection;
+the same tile as the vocabulary head with a ragged last slab, odd vocabulary
+widths and two row tiles; and short sequences whose projections (gate and up
+among them) are split over K.  The plans each case is there for are asserted.
 
 Tolerance: logits rel-RMS <= 1e-2 as everywhere on the 16-bit path (one
 rounding to 11 or 8 bits of every activation tensor of a layer)."""
@@ -18,25 +19,37 @@ import paper_2608_01821_amd as dv
 import synth
 from gpu_util import (DTYPE, TOL, Model, Sample, compare, oracle_step, random_state,
                       run_gpu_step)
+from internal import plan_gemm16
 
 pytestmark = pytest.mark.gpu
 
-# d, ffn, mode, vocab, crops (27 x 27), prompt, response
+# d, ffn, mode, vocab, crops (27 x 27), prompt, response, and the (tile, split)
+# of QKV, output, gate/up and down
 CASES = {
-    "whole-tiles": (1024, 1088, "f16", 1024, 4, 84, 72),     # 3072 rows
-    "one-past": (1024, 512, "bf16", 700, 4, 85, 72),         # 3073 rows
-    "row-skip": (1280, 1344, "f16", 700, 4, 120, 100),       # 3136 rows
-    "bands-head": (1024, 512, "f16", 1037, 5, 248, 460),     # 4353 rows
-    "head-two-tiles": (512, 64, "bf16", 1300, 1, 20, 250),
-    "split-gate-up": (1024, 512, "bf16", 700, 1, 60, 100),   # 889 rows
-    "split-3": (768, 832, "f16", 700, 1, 60, 100),
-    "short": (1536, 832, "f16", 700, 0, 7, 60),
+    "whole-tiles": (1024, 1088, "f16", 1024, 4, 84, 72,      # 3072 rows
+                    (17, 1), (12, 1), (6, 1), (12, 1)),
+    "one-past": (1024, 512, "bf16", 700, 4, 85, 72,          # 3073 rows
+                 (17, 1), (12, 1), (12, 1), (12, 1)),
+    "row-skip": (1280, 1344, "f16", 700, 4, 120, 100,        # 3136 rows
+                 (17, 1), (12, 1), (14, 1), (12, 1)),
+    "bands-head": (1024, 512, "f16", 1037, 5, 248, 460,      # 4353 rows
+                   (17, 1), (6, 1), (6, 1), (6, 1)),
+    "gate-up-down": (2048, 3072, "f16", 700, 3, 18, 100,     # 2305 rows
+                     (17, 1), (6, 1), (17, 1), (17, 3)),
+    "head-two-tiles": (512, 64, "bf16", 1300, 1, 20, 250,
+                       (12, 1), (12, 2), (12, 2), (12, 1)),
+    "split-gate-up": (1024, 512, "bf16", 700, 1, 60, 100,    # 889 rows
+                      (12, 1), (12, 4), (12, 4), (12, 1)),
+    "split-3": (768, 832, "f16", 700, 1, 60, 100,
+                (12, 1), (12, 3), (12, 1), (12, 3)),
+    "short": (1536, 832, "f16", 700, 0, 7, 60,
+              (12, 6), (12, 6), (12, 6), (12, 4)),
 }
 
 
 @pytest.mark.parametrize("name", list(CASES))
 def test_planned_products(name):
-    d, ffn, mode, vocab, crops, prompt, resp = CASES[name]
+    d, ffn, mode, vocab, crops, prompt, resp, *plans = CASES[name]
     level = 2 if crops else 0             # 0: its 49 coarsest tokens
     cfg = dataclasses.replace(
         synth.get_any_config(13), n_seqs=1, n_layers=1, d=d, n_heads=d // 128,
@@ -52,6 +65,11 @@ def test_planned_products(name):
                              head_layout=dv.DAVET_HEAD_TILED)
     s = synth.gen_sample(cfg)
     sample = Sample(cfg, max(1, crops), s["visual"][0], s["prompts"][0], mode)
+    rows = sample.sizes[level] + prompt + resp
+    for plan, product in zip(plans, ((3 * d, d, True), (d, d, False),
+                                     (2 * ffn, d, False), (d, ffn, False))):
+        p = plan_gemm16(rows, *product)
+        assert (p.tile, p.ksplit) == plan, product
     ids, masked = random_state(rng, resp, cfg.mask_id, vocab,
                                1.0 if "head" in name else 0.7)
     g_conf, g_am, g_lg = run_gpu_step(cfg, mdl, [sample], [level], ids, masked)
