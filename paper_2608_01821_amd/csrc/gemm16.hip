@@ -1094,10 +1094,15 @@ int gemm_dispatch(const GemmPlan& p, int epi, const uint16_t* A,
 // parts then moved three more (192 x 128 at 356, 4 x 4-wave 256 x 256 at 420
 // and 480: 12 % and 6 % faster), and one at 150-250 rows (8-wave 128 x 128
 // without a K split instead of 256 x 256 with two: 2-14 % faster).
-// The phased tile then took the 35 entries where it measured faster (sweep
-// of variants 6, 8, 12, 14, 16 and the phased tile, splits 1-6 and 8): gate/up
-// from 1700 rows and at 356-480, down from 2300 rows, QKV at 650-750 and
-// 1700-2300; 2-9 % each.
+// The phased tile (17) then took the entries where it measured faster (sweep of
+// variants 6, 8, 12, 14, 16 and 17, splits 1-6 and 8; 2-9 % each): gate/up from
+// 1700 rows except 2600 and at 356-480, down from 2300 rows except 2916 and at
+// 1300, QKV at 650-750, 1700-2300, 3300, 12000 and 18020, output at 18020.  Of
+// the other tiles' entries that sweep moved QKV at 300 and 356 and output at 889
+// (49 us with two splits of V6, 51 with four of V16) and 5000.  Down at 2300
+// keeps the three splits it had on an older tile (2171-2445 rows 231-245 us,
+// 258-268 on that tile, 261-273 without a split).  The edge ranges below were not
+// timed against it.
 // Because the number of row tiles and of waves of workgroups changes in
 // steps, the best plan is jagged in M; a product of M rows takes the plan of
 // the nearest sample point in log M, except in the ranges of kEdge.
@@ -1115,7 +1120,7 @@ constexpr TableShape kTable[] = {
     // gate + up: N = 2 ffn, K = d
     {24576, 4096, {{12, 1}, {14, 1}, {17, 1}, {17, 1}, {17, 1}, {12, 1}, {14, 1}, {14, 1}, {14, 1}, {14, 1}, {16, 1}, {14, 1}, {14, 1}, {17, 1}, {17, 1}, {17, 1}, {16, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}}},
     // down projection: N = d, K = ffn
-    {4096, 12288, {{12, 8}, {14, 8}, {16, 8}, {16, 8}, {8, 8}, {16, 5}, {16, 5}, {8, 5}, {16, 4}, {16, 4}, {16, 3}, {17, 2}, {14, 2}, {16, 2}, {16, 2}, {17, 1}, {17, 1}, {14, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 2}, {17, 1}, {17, 1}, {17, 1}}},
+    {4096, 12288, {{12, 8}, {14, 8}, {16, 8}, {16, 8}, {8, 8}, {16, 5}, {16, 5}, {8, 5}, {16, 4}, {16, 4}, {16, 3}, {17, 2}, {14, 2}, {16, 2}, {16, 2}, {17, 3}, {17, 1}, {14, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 1}, {17, 2}, {17, 1}, {17, 1}, {17, 1}}},
 };
 
 // Row counts just past a multiple of a point's tile height, where the point's

@@ -45,3 +45,10 @@ def test_long_products_take_the_phased_tile(d, ffn, M):
     if d >= 5120:
         assert plans["dn"] == PHASED, plans
     assert 16 not in plans.values(), plans
+
+
+@pytest.mark.parametrize("M", [2171, 2300, 2445])
+def test_down_projection_keeps_its_split(M):
+    # without the split a ninth to a twelfth slower on the same tile
+    p = plan_gemm16(M, 4096, 12288)
+    assert (p.tile, p.ksplit) == (PHASED, 3)
