@@ -18,11 +18,11 @@
 // in, the squares are summed alongside, and the finished sums are scaled by
 // 1 / sqrt(mean(x^2) + eps) of their row.
 //
-// Two launch shapes.  Small products (one workgroup of 64 x 64 outputs per CU
-// or fewer): 16 x 32 output columns per workgroup, K split over its four
-// wavefronts and summed in LDS, so that the chip fills and each chain of
-// dependent loads is a quarter as long.  Larger ones: 2 x 2 wavefronts of
-// 64 x 64 outputs, 16 flops per operand byte instead of 5.
+// Two launch shapes.  Products of fewer than 256 workgroups of 128 rows x 4 pairs
+// (128 x 128 outputs, 128 x 64 of gate and up): 16 rows x 1 pair per workgroup, K
+// split over its four wavefronts and summed in LDS, so that the chip fills and
+// each chain of dependent loads is a quarter as long.  Larger ones: 2 x 2
+// wavefronts of 64 rows x 2 pairs, 16 flops per operand byte instead of 5.
 // Measured on MI355X, a whole step (these products and the attention) against
 // 64 x 64 tiles on the vector ALUs with separate norm, rope and gather
 // launches and one attention thread per query: d = 256, 192 rows, two layers

@@ -1,7 +1,8 @@
 """The fp32 products and attention at the edges of their launch shapes,
 against the oracle: odd and unaligned feed-forward widths (K % 4 != 0 takes
 single loads), both head sizes, vocabulary and row tails, sequences shorter
-than one key block, and sizes past the switch to 64 x 64 wave tiles; norm
+than one key block, and every product on the large shape (64 x 64 wave tiles)
+in one case or another, the head with fewer live rows than its bound; norm
 gains on both sides of every fused norm.
 
 Tolerance: logits rel-RMS <= 1e-5 as everywhere on the fp32 path (sums of at
@@ -20,19 +21,34 @@ from gpu_util import (TOL, Model, Sample, compare, oracle_step, random_state,
 
 pytestmark = pytest.mark.gpu
 
-# d, heads, ffn, vocab, grid, crops, prompt, response, layers
+# d, heads, ffn, vocab, grid, crops, prompt, response, layers, and the products
+# that run on the large shape
 SHAPES = {
-    "short": (64, 1, 33, 17, 2, 1, 1, 3, 2),
-    "tails-hd64": (192, 3, 250, 333, 9, 1, 5, 21, 2),
-    "unaligned-hd128": (256, 2, 101, 301, 7, 2, 13, 37, 2),
-    "large": (768, 12, 520, 9001, 27, 3, 7, 140, 1),
-    "large-unaligned": (2048, 16, 65, 1000, 27, 3, 7, 20, 1),
+    "short": (64, 1, 33, 17, 2, 1, 1, 3, 2, ""),
+    "tails-hd64": (192, 3, 250, 333, 9, 1, 5, 21, 2, ""),
+    "unaligned-hd128": (256, 2, 101, 301, 7, 2, 13, 37, 2, ""),
+    "large": (768, 12, 520, 9001, 27, 3, 7, 140, 1, "qkv"),
+    "large-unaligned": (2048, 16, 65, 1000, 27, 3, 7, 20, 1, "qkv out down"),
+    "large-gate-up": (256, 4, 1000, 333, 27, 3, 7, 140, 1, "gate_up"),
+    "large-head": (128, 1, 101, 9001, 2, 1, 5, 400, 1, "head"),
 }
+
+
+def large_products(rows, d, ffn, vocab, resp):
+    """The launch shape's rule: 128 rows x 4 column pairs (32 columns a pair,
+    16 of gate and up) a workgroup once there are 256 of them."""
+    products = dict(qkv=(rows, 3 * d, 32), out=(rows, d, 32),
+                    gate_up=(rows, ffn, 16), down=(rows, d, 32),
+                    head=(resp, vocab, 32))
+    return {n for n, (m, cols, pair) in products.items()
+            if -(-m // 128) * -(-(-(-cols // pair)) // 4) >= 256}
 
 
 @pytest.mark.parametrize("name", list(SHAPES))
 def test_f32_step_shapes(name):
-    d, heads, ffn, vocab, grid, crops, prompt, resp, layers = SHAPES[name]
+    d, heads, ffn, vocab, grid, crops, prompt, resp, layers, large = SHAPES[name]
+    assert large_products(crops * grid * grid + prompt + resp, d, ffn, vocab,
+                          resp) == set(large.split())
     cfg = dataclasses.replace(
         synth.get_any_config(13), n_seqs=1, n_layers=layers, d=d,
         n_heads=heads, head_dim=d // heads, ffn=ffn, vocab=vocab, grid=grid,
