@@ -270,12 +270,23 @@ int launch(const F32Args& a, const SeqPack& sp, int cls, hipStream_t s) {
   const bool big = (int64_t)((a.M + 127) / 128) * ((pairs + 3) / 4) >= 256;
   const dim3 grid = big ? dim3((pairs + 3) / 4, (a.M + 127) / 128)
                         : dim3(pairs, (a.M + 15) / 16);
-  const bool vec = a.K % 4 == 0;
-#define GO(V, MI, NP, WK)                                                     \
-  hipLaunchKernelGGL((gemm_f32_kernel<EPI, NORM, GATHER, V, MI, NP, WK>),     \
-                     grid, dim3(256), 0, s, a, sp)
-  if (big) { if (vec) GO(true, 4, 2, 1); else GO(false, 4, 2, 1); }
-  else { if (vec) GO(true, 1, 1, 4); else GO(false, 1, 1, 4); }
+#define GO(V)                                                                 \
+  do {                                                                        \
+    if (big)                                                                  \
+      hipLaunchKernelGGL((gemm_f32_kernel<EPI, NORM, GATHER, V, 4, 2, 1>),    \
+                         grid, dim3(256), 0, s, a, sp);                       \
+    else                                                                      \
+      hipLaunchKernelGGL((gemm_f32_kernel<EPI, NORM, GATHER, V, 1, 1, 4>),    \
+                         grid, dim3(256), 0, s, a, sp);                       \
+  } while (0)
+  if (a.K % 4 == 0) {
+    GO(true);
+  } else if constexpr (!NORM) {
+    GO(false);
+  } else {
+    // the normed products contract over d, a multiple of 64
+    return set_error(DAVET_ESHAPE, "gemm_f32: a normed product needs K % 4 == 0");
+  }
 #undef GO
   DAVET_HIP(hipGetLastError());
   return DAVET_OK;

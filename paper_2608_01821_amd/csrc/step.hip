@@ -63,6 +63,8 @@ static Layout make_layout(const davet_model_cfg& c, int64_t tokens,
   o.argmax = take(rows * 4);
   o.argmax2 = take(rows * 4);    // the schedule loop's previous predictions
   o.X = take((size_t)tokens * c.d * 4);
+  // (A and Hm are the 16-bit path's; an fp32 workspace keeps their room, so that
+  // sizes a program has stored stay valid)
   o.A = take((size_t)tokens * c.d * es);
   o.QKV = take((size_t)tokens * 3 * c.d * es);
   o.O = take((size_t)tokens * c.d * es);
