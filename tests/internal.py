@@ -3,6 +3,8 @@ mangled names, which libdavet.so exports)."""
 
 import ctypes as C
 
+import torch           # first: the library then uses the HIP runtime torch loads
+
 import paper_2608_01821_amd as dv
 
 _L = dv.raw()
@@ -45,7 +47,6 @@ def launch_gemm16(dtype, epi, tile, ksplit, A, B, B2, out, M, N, K, ldc,
     """One product on torch tensors (None: null), tile and split as given."""
     def ptr(t):
         return None if t is None else t.data_ptr()
-    import torch
     return _launch_gemm16(
         dtype, epi, C.byref(GemmPlan(tile, ksplit)), ptr(A), ptr(B), ptr(B2),
         ptr(out), M, N, K, ldc, ptr(pos), ptr(cs), rope_cols, ptr(part),
